@@ -17,7 +17,7 @@ CALIB_LIB = os.path.join(HERE, "libfkm_calib.so")
 CALIB_SOURCES = ["calib.hip"]
 SOURCES = ["api.hip", "assign.hip", "assign_pipe_bf16.hip", "assign_pipe_f16.hip",
            "assign_smallk_bf16.hip", "assign_smallk_f16.hip", "assign_tiled.hip", "update.hip",
-           "knn_bf16.hip", "knn_f16.hip"]
+           "knn_bf16.hip", "knn_f16.hip", "knn_scan_bf16.hip", "knn_scan_f16.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -32,7 +32,7 @@ FLAGS = [
 # sources may assume no NaNs: the compiler then drops the quieting of each
 # operand before a float maximum and turns compare-and-select pairs in the
 # list insertion into single instructions.
-SOURCE_FLAGS = {"knn_bf16.hip": ["-fno-honor-nans"], "knn_f16.hip": ["-fno-honor-nans"]}
+SOURCE_FLAGS = {f: ["-fno-honor-nans"] for f in SOURCES if f.startswith("knn_")}
 
 
 def build(out: str = LIB, extra=(), sources=None) -> str:

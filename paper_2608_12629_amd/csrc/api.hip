@@ -2,6 +2,7 @@
 // host-side argument validation, workspace carving, the gfx950 check and the
 // launch sequence of each entry point.  Nothing here touches the GPU before
 // the arguments have been validated.
+#include <algorithm>
 #include <atomic>
 #include <cstring>
 #include <mutex>
@@ -296,16 +297,96 @@ static int knn_check_sizes(int64_t B, int64_t M, int64_t N, int64_t D, int64_t k
   return FKM_OK;
 }
 
-// Workspace: the database rows in the staged layout [B, Np, Dk] and their
-// scores [B, Np], Np = N rounded up to whole 128-row stages, Dk = D rounded up
-// to a multiple of 16; when Dk != D also the queries in zero-padded rows
-// [B, M, Dk].
+// How a search runs.  Few queries: the scan (knn_scan.h).  More: the list kernel
+// over `splits` shares of the rows, which fill the chip when the query blocks
+// do not.  Either needs scratch (the scan's group maxima, the shares' lists);
+// with less than that the list kernel runs unsplit, which needs none.
+struct KnnPlan {
+  bool scan;
+  KnnScanPlan sc;
+  int splits;
+  size_t scratch;  // bytes
+};
+
+static KnnScanPlan knn_scan_plan(int64_t B, int64_t M, int64_t N, int64_t Dk) {
+  KnnScanPlan p{};
+  p.tcs = Dk <= 128 ? 128 : 64;
+  const int64_t tps = p.tcs / 32, nst = (N + p.tcs - 1) / p.tcs, tiles = (N + 31) / 32;
+  // groups of at least two tiles (half the maxima to write, while a query's k
+  // groups stay small beside the scan), and few enough for the pick kernel
+  p.gs = 1;
+  while (((tiles + (1ll << p.gs) - 1) >> p.gs) > KNN_MAX_GROUPS) ++p.gs;
+  p.ngroups = (tiles + (1ll << p.gs) - 1) >> p.gs;
+  // about two workgroups per CU, whole groups each, at most KNN_SCAN_GL of them
+  const int64_t unit = (1ll << p.gs) > tps ? (1ll << p.gs) / tps : 1;
+  const int64_t qb = (M + 127) / 128 * B;
+  int64_t per = (nst * qb + 511) / 512;
+  per = (per + unit - 1) / unit * unit;
+  const int64_t most = ((int64_t)KNN_SCAN_GL << p.gs) / tps / unit * unit;
+  p.per = per < most ? per : most;
+  p.splits = (nst + p.per - 1) / p.per;
+  return p;
+}
+
+// Shares per query block: the fewest rounds of resident workgroups times the
+// stages of a share plus what starting a share, filling its empty lists and
+// merging them cost, in stages (12, or 256 with 32-entry lists, whose
+// insertions take most of the time).  Measured, D = 128: 65,536 queries in
+// 1,048,576 rows 18,291 us unsplit, 15,690 in 2 shares, 17,854 in 3; 4,096 in
+// 100,000 3,276 unsplit, 342 in 32, 423 in 48; 20,000 in 1,000,000 with k = 32
+// 27,068 unsplit, 25,712 in 3, 32,047 in 8.
+static int knn_splits(int64_t B, int64_t M, int64_t N, int64_t Dk, int k) {
+  const int64_t nst = kpad(N) / (Dk <= 128 ? 128 : 64);
+  const int64_t qpb = k <= 16 && Dk <= 128 ? 256 : 128;  // queries per workgroup
+  const int64_t slots = k <= 16 ? 512 : 256;             // resident workgroups
+  const int64_t qb = (M + qpb - 1) / qpb * B, extra = k <= 16 ? 12 : 256;
+  int64_t best = 1, cost = INT64_MAX;
+  for (int64_t s = 1; s <= KNN_MAX_SPLITS && s <= nst; ++s) {
+    const int64_t c = (qb * s + slots - 1) / slots * ((nst + s - 1) / s + extra);
+    if (c < cost) cost = c, best = s;
+  }
+  return (int)best;
+}
+
+static KnnPlan knn_plan(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, size_t scratch) {
+  KnnPlan p{};
+  p.splits = 1;
+  // Where the scan gives way (times of both at N = 1,000,003, D = 128, k = 10: M
+  // = 128 71 against 803 us, 1,024 424 / 808, 2,048 820 / 1,009, 4,096 1,608 /
+  // 1,639; N = 10,000: M = 2,048 93 / 105, 4,096 172 / 126; N = 400,000, D =
+  // 256: M = 1,024 364 / 421, 2,048 671 / 672; with 32-entry lists, one wave per
+  // SIMD, M = 4,096 at N = 1,000,003: 2,123 / 6,475).
+  const int64_t lim = k > 16 ? (Dk > 128 ? 4096 : 8192) : Dk > 128 ? 1024 : 2048;
+  if (M <= lim) {
+    p.sc = knn_scan_plan(B, M, N, Dk);
+    p.scratch = (size_t)(B * M * p.sc.ngroups) * 4;
+    // its maxima take no more than a copy of the rows would (or 64 MiB)
+    const size_t most = std::max((size_t)(B * kpad(N) * Dk) * 2, (size_t)64 << 20);
+    p.scan = p.scratch <= std::min(scratch, most);
+    if (p.scan) return p;
+  }
+  p.splits = knn_splits(B, M, N, Dk, k);
+  p.scratch = p.splits > 1 ? (size_t)(B * M * p.splits * k) * 8 : 0;
+  if (p.scratch > scratch) {
+    p.splits = 1;
+    p.scratch = 0;
+  }
+  return p;
+}
+
+// Workspace.  Dk = D rounded up to a multiple of 16, Np = N rounded up to whole
+// 128-row stages.  Dk != D: the database rows padded to [B, Np, Dk], their
+// scores [B, Np] and the queries padded to [B, M, Dk], then the plan's scratch.
+// Dk == D: the rows are read in place; scores, the rows of the last partial
+// stage, then the scratch, all within the size of a copy of the rows or more.
+// `fixed` is what a search needs at the least.
 struct KnnWs {
   void* chat;
   float* cinit;
   void* qpad;
+  char* scratch;
+  size_t scratch_at, fixed;
   int64_t Np, Dk;
-  size_t total;
 };
 static KnnWs knn_carve(void* base, int64_t B, int64_t M, int64_t N, int64_t D) {
   KnnWs w{};
@@ -318,16 +399,22 @@ static KnnWs knn_carve(void* base, int64_t B, int64_t M, int64_t N, int64_t D) {
     o = align_up(o + bytes);
     return r;
   };
-  w.chat = take((size_t)(B * w.Np * w.Dk) * 2);
+  const size_t rows = (size_t)(B * w.Np * w.Dk) * 2;
+  const bool direct = w.Dk == D;
   w.cinit = (float*)take((size_t)(B * w.Np) * 4);
-  w.qpad = take(w.Dk != D ? (size_t)(B * M * w.Dk) * 2 : 0);
-  w.total = o;
+  w.chat = take(direct ? (size_t)(B * ASSIGN_KPAD * w.Dk) * 2 : rows);
+  w.qpad = take(direct ? 0 : (size_t)(B * M * w.Dk) * 2);
+  w.scratch_at = o;
+  w.scratch = p ? p + o : nullptr;
+  w.fixed = direct ? o + align_up(rows - (size_t)(B * ASSIGN_KPAD * w.Dk) * 2) : o;
   return w;
 }
 
 size_t kmeans_knn_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t D, int k, int xdtype) {
   if (knn_check_sizes(B, M, N, D, k, xdtype) != FKM_OK) return 0;
-  return knn_carve(nullptr, B, M, N, D).total;
+  const KnnWs w = knn_carve(nullptr, B, M, N, D);
+  const size_t want = w.scratch_at + knn_plan(B, M, N, w.Dk, k, SIZE_MAX).scratch;
+  return want > w.fixed ? want : w.fixed;
 }
 
 int kmeans_knn(const void* Q, const void* R, int xdtype, int64_t B, int64_t M, int64_t N, int64_t D,
@@ -335,21 +422,34 @@ int kmeans_knn(const void* Q, const void* R, int xdtype, int64_t B, int64_t M, i
   int rc;
   if ((rc = check_ptrs({Q, R, nbr_idx, nbr_dist}))) return rc;
   if ((rc = knn_check_sizes(B, M, N, D, k, xdtype))) return rc;
-  if (!ws || !aligned16(ws) || ws_bytes < knn_carve(nullptr, B, M, N, D).total)
+  if (!ws || !aligned16(ws) || ws_bytes < knn_carve(nullptr, B, M, N, D).fixed)
     return FKM_ERR_WORKSPACE;
   if ((rc = check_device())) return rc;
   const KnnWs w = knn_carve(ws, B, M, N, D);
   hipStream_t s = (hipStream_t)stream;
+  const bool bf = xdtype == DT_BF16, direct = w.Dk == D;
+  const KnnPlan p = knn_plan(B, M, N, w.Dk, k, ws_bytes - w.scratch_at);
   const void* Qk = Q;
-  if (w.Dk != D) {
+  KnnRows rows{R, w.chat, w.cinit, N, N, w.Np};
+  if (!direct) {
     if ((rc = hip_status(launch_pad_rows(Q, B * M, D, w.Dk, 2, w.qpad, s)))) return rc;
     Qk = w.qpad;
+    if ((rc = hip_status((bf ? launch_knn_prep_bf16 : launch_knn_prep_f16)(R, B, N, w.Np, D, w.Dk,
+                                                                            w.chat, w.cinit, s))))
+      return rc;
+    rows = KnnRows{w.chat, nullptr, w.cinit, N, w.Np, w.Np};
   }
-  if (xdtype == DT_BF16)
-    return hip_status(launch_knn_bf16(Qk, R, B, M, N, D, w.Dk, k, w.chat, w.cinit, w.Np, nbr_idx,
-                                      nbr_dist, s));
-  return hip_status(launch_knn_f16(Qk, R, B, M, N, D, w.Dk, k, w.chat, w.cinit, w.Np, nbr_idx,
-                                   nbr_dist, s));
+  if (p.scan)
+    return hip_status((bf ? launch_knn_scan_bf16 : launch_knn_scan_f16)(
+        Qk, rows.rows, B, M, N, rows.nrows, w.Dk, k, p.sc, (float*)w.scratch, nbr_idx, nbr_dist, s));
+  if (direct &&
+      (rc = hip_status((bf ? launch_knn_norm_bf16 : launch_knn_norm_f16)(R, B, N, w.Np, w.Dk,
+                                                                          w.cinit, w.chat, s))))
+    return rc;
+  const size_t lists = (size_t)(B * M * p.splits * k);
+  const KnnSplit sp{p.splits, (int32_t*)w.scratch, (float*)w.scratch + lists};
+  return hip_status((bf ? launch_knn_bf16 : launch_knn_f16)(Qk, rows, B, M, w.Dk, k, sp, nbr_idx,
+                                                             nbr_dist, s));
 }
 
 const char* kmeans_status_string(int status) {

@@ -51,6 +51,24 @@ __device__ inline float chunk_sumsq(const uint4& q, float acc) {
   return acc;
 }
 
+// Sum of squares of CPL chunks: each chunk in element order, then the chunks
+// pairwise (a chain over a 128-element half loses about twice as much).
+template <int DT, int CPL, typename Get>
+__device__ inline float tree_sumsq_of(Get chunk) {
+  float s[CPL];
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) s[c] = chunk_sumsq<DT>(chunk(c), 0.f);
+#pragma unroll
+  for (int d = 1; d < CPL; d *= 2)
+#pragma unroll
+    for (int c = 0; c + d < CPL; c += 2 * d) s[c] += s[c + d];
+  return s[0];
+}
+template <int DT, int CPL>
+__device__ inline float tree_sumsq(const uint4 (&a)[CPL]) {
+  return tree_sumsq_of<DT, CPL>([&](int c) { return a[c]; });
+}
+
 // One centroid row for the assignment: c^ = round(c) to the storage type
 // into out (D elements) and -|c^|^2 / 2 into *cinit (a padding row: zeros and
 // -FLT_MAX), by one wave: the squares are summed lane-strided and then by a

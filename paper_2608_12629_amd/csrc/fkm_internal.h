@@ -202,13 +202,48 @@ hipError_t launch_sums(const void* X, int dt, const Workspace& w, int64_t B, int
 hipError_t launch_combine(const Workspace& w, int64_t nch, const float* C_prev, int64_t B,
                           int64_t K, int64_t D, float* C_out, int32_t* counts,
                           const NextStep& nx, hipStream_t s);
-// KNN: R rows of Din elements; Q rows and the staged rows of D >= Din (a multiple of 16)
-hipError_t launch_knn_bf16(const void* Q, const void* R, int64_t B, int64_t M, int64_t N,
-                           int64_t Din, int64_t D, int k, void* chat, float* cinit, int64_t Np,
-                           int32_t* nbr_idx, float* nbr_dist, hipStream_t s);
-hipError_t launch_knn_f16(const void* Q, const void* R, int64_t B, int64_t M, int64_t N,
-                          int64_t Din, int64_t D, int k, void* chat, float* cinit, int64_t Np,
-                          int32_t* nbr_idx, float* nbr_dist, hipStream_t s);
+// KNN.  The database rows as the list kernel streams them: whole stages from
+// `rows` ([B, nrows, D]) and, with a tail, the last stages from the padded
+// [B, ASSIGN_KPAD, D] copy of the rows past the last whole stage; cinit
+// [B, Np] their -1/2 squared norms.
+struct KnnRows {
+  const void* rows;
+  const void* tail;
+  const float* cinit;
+  int64_t N, nrows, Np;
+};
+// The list kernel's split of the rows: `splits` shares per query block, whose
+// lists go to idx / v ([B, M, splits, k]) and are merged.
+struct KnnSplit {
+  int splits;
+  int32_t* idx;
+  float* v;
+};
+// The scan's split (knn_scan.h): stages of tcs rows, `per` to a workgroup,
+// groups of 2^gs 32-row tiles.
+struct KnnScanPlan {
+  int64_t tcs, per, splits, ngroups;
+  int gs;
+};
+// Groups of a query whose best scores the pick kernel holds in LDS, and the
+// groups one scan workgroup collects in LDS before writing them out.
+constexpr int KNN_MAX_GROUPS = 8192;
+constexpr int KNN_SCAN_GL = 24;
+constexpr int KNN_MAX_SPLITS = 64;
+#define FKM_KNN_DECL(T)                                                                            \
+  hipError_t launch_knn_norm_##T(const void* R, int64_t B, int64_t N, int64_t Np, int64_t D,       \
+                                 float* cinit, void* tail, hipStream_t s);                         \
+  hipError_t launch_knn_prep_##T(const void* R, int64_t B, int64_t N, int64_t Np, int64_t Din,     \
+                                 int64_t D, void* chat, float* cinit, hipStream_t s);              \
+  hipError_t launch_knn_##T(const void* Q, const KnnRows& r, int64_t B, int64_t M, int64_t D,      \
+                            int k, const KnnSplit& sp, int32_t* nbr_idx, float* nbr_dist,          \
+                            hipStream_t s);                                                        \
+  hipError_t launch_knn_scan_##T(const void* Q, const void* R, int64_t B, int64_t M, int64_t N,    \
+                                 int64_t nrows, int64_t D, int k, const KnnScanPlan& p,            \
+                                 float* gmax, int32_t* nbr_idx, float* nbr_dist, hipStream_t s);
+FKM_KNN_DECL(bf16)
+FKM_KNN_DECL(f16)
+#undef FKM_KNN_DECL
 hipError_t launch_assign_tiled(const void* X, int dt, const Workspace& w, int64_t B, int64_t N,
                                int64_t D, int32_t* idx, float* min_dist, hipStream_t s);
 hipError_t launch_pad_rows(const void* src, int64_t rows, int64_t D, int64_t Dk, int elem_bytes,

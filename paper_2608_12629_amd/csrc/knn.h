@@ -7,12 +7,15 @@
 // distance matrix is never stored.  Instantiated once per storage type in
 // knn_bf16.hip and knn_f16.hip.
 //
-// Queries play the points' role: each wave keeps 32 queries in registers
-// (one 32-column MFMA tile).  Database rows play the centroids' role: a
-// preparation pass copies them into the padded, staged layout with their
-// -|r|^2/2 scores (the rows are already in the storage type, so nothing is
-// rounded), and they stream through LDS in the assignment kernel's stages
-// (direct L2-to-LDS loads, XOR-swizzled rows, double buffering).
+// Queries play the points' role: each wave keeps 32 or 64 queries in registers
+// (32-column MFMA tiles).  Database rows play the centroids' role: a first
+// pass writes their -|r|^2/2 (the rows are already in the storage type, so
+// nothing is rounded; rows whose width is not a multiple of 16 are copied into
+// padded ones), and they stream through LDS in the assignment kernel's stages
+// (direct L2-to-LDS loads, XOR-swizzled rows, double buffering).  When the
+// query blocks do not fill the chip, each takes the rows in several shares
+// (blockIdx.z) and knn_merge_kernel merges their lists.  Few queries go to
+// knn_scan.h instead.
 //
 // Top-k.  Lane 32 h + n holds, for query n, the 16 scores of rows
 // 8 q + 4 h + r of each 32-row tile, and keeps its own list of the KMAX best
@@ -28,6 +31,44 @@
 #include "assign_pipe.h"
 
 namespace fkm {
+
+// -|r|^2/2 of every database row, read in the stages' layout through LDS (one
+// stage per workgroup, whole rows per load), and the rows of the last, partial
+// stages copied to `tail` (ASSIGN_KPAD rows per instance from row `ntail0` on;
+// zero rows with score -FLT_MAX past N), so that the search streams every
+// other stage straight from the caller's array.  Replaces a copy of all rows:
+// 275 -> 41 us at 1,048,576 x 128 bf16 (6.5 TB/s).
+template <int DT, int CPL>
+__global__ __launch_bounds__(256) void knn_norm_kernel(const uint4* __restrict__ R, int N, int Np,
+                                                       int ntail0, float* __restrict__ cinit,
+                                                       uint4* __restrict__ tail) {
+  using L = PipeLayout<CPL>;
+  constexpr int LOADS = L::TCS * L::RCP / ASSIGN_THREADS;
+  __shared__ __attribute__((aligned(16))) char buf[L::CHUNKS];
+  const int b = blockIdx.y, tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 31, h = lane >> 5;
+  R += (size_t)b * N * L::RC;
+  PipeOffsets<CPL, LOADS> o;
+  pipe_offsets<CPL, LOADS>(o, tid, n, h);
+  const int row0 = blockIdx.x * L::TCS;
+  pipe_issue_rows<CPL, LOADS>(R, row0, N, tid, buf);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (wave >= L::TILES) return;
+  uint4 a[CPL];
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) a[c] = lds_at<uint4>(buf, o.a[c] + wave * L::TILE, 0);
+  float ss = tree_sumsq<DT, CPL>(a);
+  ss += __shfl_xor(ss, 32);
+  const int row = row0 + wave * 32 + n;
+  if (h == 0) cinit[(size_t)b * Np + row] = row < N ? -0.5f * ss : -0x1.fffffep127f;
+  if (row >= ntail0) {
+    uint4* t = tail + ((size_t)b * ASSIGN_KPAD + (row - ntail0)) * L::RC + h * CPL;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) t[c] = row < N ? a[c] : make_uint4(0, 0, 0, 0);
+  }
+}
 
 // Database rows to the staged layout: row j of each instance to chat (padded to
 // Np rows: zero rows with score -FLT_MAX; rows of Din elements widened to D
@@ -164,13 +205,20 @@ __device__ __forceinline__ void knn_update(const f32x16& acc, int base, float (&
 template <int DT, int CPL, int NSUB, int KMAX, int LOADS>
 __device__ __forceinline__ void knn_stage(int st, int nst, char* cur, char* nxt,
                                           const PipeOffsets<CPL, LOADS>& o,
-                                          const uint4 (&xr)[NSUB][CPL], const u32x4* chat4,
+                                          const uint4 (&xr)[NSUB][CPL], const u32x4* rows,
+                                          const u32x4* tail, int nfull,
                                           const float* cinit, int tid, int h,
                                           float (&v)[NSUB][KMAX], int (&ix)[NSUB][KMAX]) {
   using L = PipeLayout<CPL>;
   const bool more = st + 1 < nst;
   float nn = 0.f;
-  if (more) nn = pipe_issue_stage<CPL, LOADS>(chat4, cinit, st + 1, tid, o, nxt);
+  if (more) {
+    // stages from nfull on come from the padded copy (a scalar select, no branch)
+    const u32x4* src = st + 1 < nfull ? rows + (size_t)(st + 1) * (L::TCS * L::RC)
+                                      : tail + (size_t)(st + 1 - nfull) * (L::TCS * L::RC);
+    pipe_issue_dma<CPL, LOADS>(src, 0, tid, o, nxt);
+    nn = pipe_score<CPL>(cinit, st + 1, tid);
+  }
   if constexpr (KMAX > 16) {
     static_assert(NSUB == 1, "32-entry lists keep one query tile per wave");
     f32x16 acc[2][1];
@@ -203,8 +251,9 @@ __device__ __forceinline__ void knn_stage(int st, int nst, char* cur, char* nxt,
 // more of the LDS than the matrix pipes take in).
 template <int DT, int CPL, int NSUB, int KMAX>
 __global__ __launch_bounds__(ASSIGN_THREADS, KMAX <= 16 ? 2 : 1) void knn_kernel(
-    const uint4* __restrict__ Q, const uint4* __restrict__ chat, const float* __restrict__ cinit,
-    int M, int Np, int k, int32_t* __restrict__ nbr_idx, float* __restrict__ nbr_dist) {
+    const uint4* __restrict__ Q, const uint4* __restrict__ rows, const uint4* __restrict__ tail,
+    const float* __restrict__ cinit, int M, int nrows, int nfull, int Np, int per, int k,
+    int32_t* __restrict__ nbr_idx, float* __restrict__ nbr_dist) {
   using L = PipeLayout<CPL>;
   constexpr int RC = L::RC;
   constexpr int LOADS = L::TCS * L::RCP / ASSIGN_THREADS;
@@ -219,13 +268,18 @@ __global__ __launch_bounds__(ASSIGN_THREADS, KMAX <= 16 ? 2 : 1) void knn_kernel
   const int lane = tid & 63, wave = tid >> 6;
   const int n = lane & 31, h = lane >> 5;
   Q += (size_t)b * M * RC;
-  const u32x4* chat4 = reinterpret_cast<const u32x4*>(chat) + (size_t)b * Np * RC;
+  const u32x4* rows4 = reinterpret_cast<const u32x4*>(rows) + (size_t)b * nrows * RC;
+  const u32x4* tail4 = reinterpret_cast<const u32x4*>(tail) + (size_t)b * ASSIGN_KPAD * RC;
   cinit += (size_t)b * Np;
-  const int nst = Np / L::TCS;
+  // this workgroup's share of the stages (`per` of them; all without a split)
+  const int sp = blockIdx.z, st0 = sp * per, nst = min(st0 + per, Np / L::TCS);
 
   PipeOffsets<CPL, LOADS> o;
   pipe_offsets<CPL, LOADS>(o, tid, n, h);
-  float nn = pipe_issue_stage<CPL, LOADS>(chat4, cinit, 0, tid, o, buf0);
+  pipe_issue_dma<CPL, LOADS>(st0 < nfull ? rows4 + (size_t)st0 * (L::TCS * RC)
+                                         : tail4 + (size_t)(st0 - nfull) * (L::TCS * RC),
+                             0, tid, o, buf0);
+  const float nn = pipe_score<CPL>(cinit, st0, tid);
 
   const int q0 = blockIdx.x * QPB + wave * QPW + n;  // this lane's query of tile 0
   uint4 xr[NSUB][CPL];
@@ -233,12 +287,10 @@ __global__ __launch_bounds__(ASSIGN_THREADS, KMAX <= 16 ? 2 : 1) void knn_kernel
 #pragma unroll
   for (int p = 0; p < NSUB; ++p) {
     const int qt = q0 + 32 * p;
-    float a = 0.f;
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
+    for (int c = 0; c < CPL; ++c)
       xr[p][c] = qt < M ? Q[(size_t)qt * RC + h * CPL + c] : make_uint4(0, 0, 0, 0);
-      a = chunk_sumsq<DT>(xr[p][c], a);
-    }
+    const float a = tree_sumsq<DT, CPL>(xr[p]);
     ss[p] = a + __shfl_xor(a, 32);
   }
 
@@ -255,14 +307,16 @@ __global__ __launch_bounds__(ASSIGN_THREADS, KMAX <= 16 ? 2 : 1) void knn_kernel
   lds_at<float>(buf0, o.n_store, 0) = nn;
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  int st = 0;
+  int st = st0;
   for (; st + 2 <= nst; st += 2) {  // two stages per trip: each buffer is a fixed array
-    knn_stage<DT, CPL, NSUB, KMAX, LOADS>(st, nst, buf0, buf1, o, xr, chat4, cinit, tid, h, v, ix);
-    knn_stage<DT, CPL, NSUB, KMAX, LOADS>(st + 1, nst, buf1, buf0, o, xr, chat4, cinit, tid, h, v,
-                                          ix);
+    knn_stage<DT, CPL, NSUB, KMAX, LOADS>(st, nst, buf0, buf1, o, xr, rows4, tail4, nfull, cinit,
+                                          tid, h, v, ix);
+    knn_stage<DT, CPL, NSUB, KMAX, LOADS>(st + 1, nst, buf1, buf0, o, xr, rows4, tail4, nfull,
+                                          cinit, tid, h, v, ix);
   }
   if (st < nst)
-    knn_stage<DT, CPL, NSUB, KMAX, LOADS>(st, nst, buf0, buf1, o, xr, chat4, cinit, tid, h, v, ix);
+    knn_stage<DT, CPL, NSUB, KMAX, LOADS>(st, nst, buf0, buf1, o, xr, rows4, tail4, nfull, cinit,
+                                          tid, h, v, ix);
 
 #pragma unroll
   for (int p = 0; p < NSUB; ++p) {
@@ -275,15 +329,63 @@ __global__ __launch_bounds__(ASSIGN_THREADS, KMAX <= 16 ? 2 : 1) void knn_kernel
     }
     const int qt = q0 + 32 * p;
     if (h == 0 && qt < M) {
-      int32_t* oi = nbr_idx + ((size_t)b * M + qt) * k;
-      float* od = nbr_dist + ((size_t)b * M + qt) * k;
+      // with a split: the share's list (its scores as they are) beside the others
+      const bool part = gridDim.z > 1;
+      const size_t at = (((size_t)b * M + qt) * gridDim.z + sp) * k;
+      int32_t* oi = nbr_idx + at;
+      float* od = nbr_dist + at;
 #pragma unroll
       for (int t = 0; t < KMAX; ++t) {
         if (t < k) {
           oi[t] = ix[p][t];
-          od[t] = __builtin_fmaxf(__builtin_fmaf(-2.f, v[p][t], ss[p]), 0.f);
+          od[t] = part ? v[p][t] : __builtin_fmaxf(__builtin_fmaf(-2.f, v[p][t], ss[p]), 0.f);
         }
       }
+    }
+  }
+}
+
+// The lists of a query's `splits` (at most 64) shares into one: one wave per
+// query, lane l at the head of list l; k times the best head by (score, then
+// lower index) is taken and its lane moves on.
+template <int DT, int CPL>
+__global__ __launch_bounds__(256) void knn_merge_kernel(const uint4* __restrict__ Q, int64_t MB,
+                                                        int splits, int k,
+                                                        const int32_t* __restrict__ pidx,
+                                                        const float* __restrict__ pv,
+                                                        int32_t* __restrict__ nbr_idx,
+                                                        float* __restrict__ nbr_dist) {
+  const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (q >= MB) return;
+  // |q|^2 as the search sums it, half by half
+  const uint4* qr = Q + q * (2 * CPL);
+  const float qn = tree_sumsq_of<DT, CPL>([&](int c) { return qr[c]; }) +
+                   tree_sumsq_of<DT, CPL>([&](int c) { return qr[CPL + c]; });
+  const size_t base = ((size_t)q * splits + lane) * k;
+  const bool has = lane < splits;
+  int at = 0;
+  float v = has ? pv[base] : -__builtin_inff();
+  int i = has ? pidx[base] : 0x7fffffff;
+  for (int t = 0; t < k; ++t) {
+    float m = v;
+    int im = i;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const float mo = __shfl_xor(m, d);
+      const int io = __shfl_xor(im, d);
+      const bool take = mo > m || (mo == m && io < im);
+      m = take ? mo : m;
+      im = take ? io : im;
+    }
+    if (lane == 0) {
+      nbr_idx[q * k + t] = im;
+      nbr_dist[q * k + t] = __builtin_fmaxf(__builtin_fmaf(-2.f, m, qn), 0.f);
+    }
+    if (has && i == im && v == m) {  // this lane's head was taken (indices are distinct)
+      ++at;
+      v = at < k ? pv[base + at] : -__builtin_inff();
+      i = at < k ? pidx[base + at] : 0x7fffffff;
     }
   }
 }
@@ -294,25 +396,33 @@ template <int CPL, int KMAX>
 constexpr int knn_nsub() { return KMAX <= 16 && CPL <= 8 ? 2 : 1; }
 
 template <int DT, int CPL, int KMAX>
-hipError_t launch_knn_cpl(const void* Q, const void* chat, const float* cinit, int64_t B,
-                          int64_t M, int64_t Np, int k, int32_t* nbr_idx, float* nbr_dist,
-                          hipStream_t s) {
+hipError_t launch_knn_cpl(const void* Q, const KnnRows& r, int64_t B, int64_t M, int k,
+                          const KnnSplit& sp, int32_t* nbr_idx, float* nbr_dist, hipStream_t s) {
+  using L = PipeLayout<CPL>;
   constexpr int NSUB = knn_nsub<CPL, KMAX>();
   constexpr int QPB = 4 * 32 * NSUB;
-  const dim3 grid((unsigned)((M + QPB - 1) / QPB), (unsigned)B), block(ASSIGN_THREADS);
-  knn_kernel<DT, CPL, NSUB, KMAX><<<grid, block, 0, s>>>((const uint4*)Q, (const uint4*)chat,
-                                                         cinit, (int)M, (int)Np, k, nbr_idx,
-                                                         nbr_dist);
+  const int nst = (int)(r.Np / L::TCS);
+  const int per = (int)((nst + sp.splits - 1) / sp.splits);
+  const int splits = (nst + per - 1) / per;
+  const dim3 grid((unsigned)((M + QPB - 1) / QPB), (unsigned)B, (unsigned)splits);
+  const bool part = splits > 1;
+  knn_kernel<DT, CPL, NSUB, KMAX><<<grid, dim3(ASSIGN_THREADS), 0, s>>>(
+      (const uint4*)Q, (const uint4*)r.rows, (const uint4*)r.tail, r.cinit, (int)M, (int)r.nrows,
+      (int)(r.tail ? r.N / L::TCS : nst), (int)r.Np, per, k, part ? sp.idx : nbr_idx,
+      part ? sp.v : nbr_dist);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !part) return e;
+  knn_merge_kernel<DT, CPL><<<dim3((unsigned)((B * M + 3) / 4)), 256, 0, s>>>(
+      (const uint4*)Q, B * M, splits, k, sp.idx, sp.v, nbr_idx, nbr_dist);
   return hipGetLastError();
 }
 
 template <int DT, int KMAX>
-hipError_t launch_knn_k(const void* Q, const void* chat, const float* cinit, int64_t B, int64_t M,
-                        int64_t Np, int64_t D, int k, int32_t* nbr_idx, float* nbr_dist,
-                        hipStream_t s) {
+hipError_t launch_knn_k(const void* Q, const KnnRows& r, int64_t B, int64_t M, int64_t D, int k,
+                        const KnnSplit& sp, int32_t* nbr_idx, float* nbr_dist, hipStream_t s) {
   switch (D / 16) {
 #define FKM_KNN_CASE(c) \
-  case c: return launch_knn_cpl<DT, c, KMAX>(Q, chat, cinit, B, M, Np, k, nbr_idx, nbr_dist, s);
+  case c: return launch_knn_cpl<DT, c, KMAX>(Q, r, B, M, k, sp, nbr_idx, nbr_dist, s);
     FKM_KNN_CASE(1) FKM_KNN_CASE(2) FKM_KNN_CASE(3) FKM_KNN_CASE(4)
     FKM_KNN_CASE(5) FKM_KNN_CASE(6) FKM_KNN_CASE(7) FKM_KNN_CASE(8)
     FKM_KNN_CASE(9) FKM_KNN_CASE(10) FKM_KNN_CASE(11) FKM_KNN_CASE(12)
@@ -322,22 +432,49 @@ hipError_t launch_knn_k(const void* Q, const void* chat, const float* cinit, int
   }
 }
 
-// prep + search for one storage type; k <= KNN_MAX_K.  R has rows of Din
-// elements, Q (already padded) and the staged rows have D, D % 16 == 0, D <= 256.
+// The norms of the database rows, read in place, and the tail copy.
 template <int DT>
-hipError_t launch_knn_dt(const void* Q, const void* R, int64_t B, int64_t M, int64_t N,
-                         int64_t Din, int64_t D, int k, void* chat, float* cinit, int64_t Np,
-                         int32_t* nbr_idx, float* nbr_dist, hipStream_t s) {
-  if (D % 16 != 0 || D > 256 || Din > D || k < 1 || k > KNN_MAX_K || Np % ASSIGN_KPAD != 0)
-    return hipErrorInvalidValue;
+hipError_t launch_knn_norm(const void* R, int64_t B, int64_t N, int64_t Np, int64_t D,
+                           float* cinit, void* tail, hipStream_t s) {
+  switch (D / 16) {
+#define FKM_KNN_CASE(c)                                                                            \
+  case c: {                                                                                        \
+    using L = PipeLayout<c>;                                                                       \
+    knn_norm_kernel<DT, c><<<dim3((unsigned)(Np / L::TCS), (unsigned)B), 256, 0, s>>>(             \
+        (const uint4*)R, (int)N, (int)Np, (int)(N / L::TCS * L::TCS), cinit, (uint4*)tail);        \
+    break;                                                                                         \
+  }
+    FKM_KNN_CASE(1) FKM_KNN_CASE(2) FKM_KNN_CASE(3) FKM_KNN_CASE(4)
+    FKM_KNN_CASE(5) FKM_KNN_CASE(6) FKM_KNN_CASE(7) FKM_KNN_CASE(8)
+    FKM_KNN_CASE(9) FKM_KNN_CASE(10) FKM_KNN_CASE(11) FKM_KNN_CASE(12)
+    FKM_KNN_CASE(13) FKM_KNN_CASE(14) FKM_KNN_CASE(15) FKM_KNN_CASE(16)
+#undef FKM_KNN_CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// The padded copy of database rows of Din elements in rows of D (chat), and their scores.
+template <int DT>
+hipError_t launch_knn_prep(const void* R, int64_t B, int64_t N, int64_t Np, int64_t Din, int64_t D,
+                           void* chat, float* cinit, hipStream_t s) {
   knn_prep_kernel<DT><<<dim3((unsigned)((B * Np + 3) / 4)), 256, 0, s>>>(
       (const uint16_t*)R, B, (int)N, (int)Np, (int)Din, (int)D, (uint16_t*)chat, cinit);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (k <= 8) return launch_knn_k<DT, 8>(Q, chat, cinit, B, M, Np, D, k, nbr_idx, nbr_dist, s);
-  if (k <= 10) return launch_knn_k<DT, 10>(Q, chat, cinit, B, M, Np, D, k, nbr_idx, nbr_dist, s);
-  if (k <= 16) return launch_knn_k<DT, 16>(Q, chat, cinit, B, M, Np, D, k, nbr_idx, nbr_dist, s);
-  return launch_knn_k<DT, KNN_MAX_K>(Q, chat, cinit, B, M, Np, D, k, nbr_idx, nbr_dist, s);
+  return hipGetLastError();
+}
+
+// The search for one storage type over prepared rows; k <= KNN_MAX_K, rows of
+// D elements, D % 16 == 0, D <= 256.
+template <int DT>
+hipError_t launch_knn_dt(const void* Q, const KnnRows& r, int64_t B, int64_t M, int64_t D, int k,
+                         const KnnSplit& sp, int32_t* nbr_idx, float* nbr_dist, hipStream_t s) {
+  if (D % 16 != 0 || D > 256 || k < 1 || k > KNN_MAX_K || r.Np % ASSIGN_KPAD != 0 ||
+      sp.splits < 1 || sp.splits > KNN_MAX_SPLITS)
+    return hipErrorInvalidValue;
+  if (k <= 8) return launch_knn_k<DT, 8>(Q, r, B, M, D, k, sp, nbr_idx, nbr_dist, s);
+  if (k <= 10) return launch_knn_k<DT, 10>(Q, r, B, M, D, k, sp, nbr_idx, nbr_dist, s);
+  if (k <= 16) return launch_knn_k<DT, 16>(Q, r, B, M, D, k, sp, nbr_idx, nbr_dist, s);
+  return launch_knn_k<DT, KNN_MAX_K>(Q, r, B, M, D, k, sp, nbr_idx, nbr_dist, s);
 }
 
 }  // namespace fkm

@@ -1,12 +1,21 @@
-// knn_f16.hip -- KNN search for f16 rows.
+// knn_f16.hip -- KNN search for f16 rows: the list kernel and its preparation.
 #include "knn.h"
 
 namespace fkm {
 
-hipError_t launch_knn_f16(const void* Q, const void* R, int64_t B, int64_t M, int64_t N,
-                         int64_t Din, int64_t D, int k, void* chat, float* cinit, int64_t Np,
-                         int32_t* nbr_idx, float* nbr_dist, hipStream_t s) {
-  return launch_knn_dt<DT_F16>(Q, R, B, M, N, Din, D, k, chat, cinit, Np, nbr_idx, nbr_dist, s);
+hipError_t launch_knn_norm_f16(const void* R, int64_t B, int64_t N, int64_t Np, int64_t D,
+                               float* cinit, void* tail, hipStream_t s) {
+  return launch_knn_norm<DT_F16>(R, B, N, Np, D, cinit, tail, s);
+}
+
+hipError_t launch_knn_prep_f16(const void* R, int64_t B, int64_t N, int64_t Np, int64_t Din,
+                               int64_t D, void* chat, float* cinit, hipStream_t s) {
+  return launch_knn_prep<DT_F16>(R, B, N, Np, Din, D, chat, cinit, s);
+}
+
+hipError_t launch_knn_f16(const void* Q, const KnnRows& r, int64_t B, int64_t M, int64_t D, int k,
+                          const KnnSplit& sp, int32_t* nbr_idx, float* nbr_dist, hipStream_t s) {
+  return launch_knn_dt<DT_F16>(Q, r, B, M, D, k, sp, nbr_idx, nbr_dist, s);
 }
 
 }  // namespace fkm

@@ -108,6 +108,74 @@ def test_knn_parity(km, oracle, shape):
     say(f"  positions differing from the oracle's order (near-ties): {differ} of {B * M * k}")
 
 
+# Sizes at the edges of the routes: the scan's group sizes, splits and partial
+# groups (few queries), and the list kernel's shares (more queries).
+ROUTES = [
+    (1, 1, 32, 16, 32, "bf16"),           # one tile, one group, k = N
+    (1, 1, 33, 128, 32, "f16"),           # a row in the second tile, fewer groups than k
+    (1, 3, 4095, 144, 32, "bf16"),        # 64-row stages, every group chosen by some query
+    (2, 129, 20_001, 64, 16, "f16"),      # two query blocks, ragged last group, batched
+    (1, 5, 300_007, 32, 10, "bf16"),      # 4,689 groups of two tiles
+    (1, 2, 530_000, 16, 9, "f16"),        # more than 8,192 pairs of tiles: groups of four
+    (1, 40, 9_000, 40, 12, "bf16"),       # padded rows (40 -> 48)
+    (1, 2_049, 1_500, 32, 10, "bf16"),    # the list kernel in shares
+    (1, 1_025, 900, 144, 20, "f16"),      # the scan at k > 16 past the limit of smaller k
+    (2, 2_100, 700, 24, 16, "f16"),       # shares, padded rows, batched
+]
+
+
+@pytest.mark.parametrize("shape", ROUTES, ids=lambda s: "x".join(map(str, s)))
+def test_knn_routes(km, oracle, shape):
+    """Every route against fp64, and the unsplit list kernel (what a workspace
+    of a copy of the rows leaves room for) against the others bit for bit
+    where the rows are read in place."""
+    B, M, N, D, k, dt = shape
+    Q, R = _data(B, M, N, D, dt, seed=M + N + k)
+    say(f"[knn routes] B={B} M={M} N={N} D={D} k={k} {dt}")
+    Qd, Rd = Q.cuda(), R.cuda()
+    gi, gd = km.kmeans_knn(Qd, Rd, k)
+    torch.cuda.synchronize()
+    q64, r64 = Q.double(), R.double()
+    for b in range(B):
+        dist = ((q64[b] ** 2).sum(-1)[:, None] - 2 * q64[b] @ r64[b].T + (r64[b] ** 2).sum(-1)[None])
+        want, _ = dist.topk(k, 1, largest=False)
+        i = gi[b].cpu().long()
+        assert (i >= 0).all() and (i < N).all()
+        assert all(len(set(r)) == k for r in i.tolist())
+        scale = (q64[b] ** 2).sum(-1)[:, None]
+        got = dist.gather(1, i)
+        # the scores' fp32 rounding: D products and sums of up to |q||r| each
+        tol = 4 * (D + 8) * 2.0 ** -24 * (scale + (r64[b] ** 2).sum(-1).max())
+        assert ((got - want).abs() <= tol).all(), float(((got - want).abs() / tol).max())
+        assert ((gd[b].cpu().double() - got.clamp(min=0)).abs() <= tol).all()
+    # the least workspace: row scores and copies, no room for shares or maxima beyond a row copy
+    up = lambda v: (v + 255) // 256 * 256  # noqa: E731
+    Np, Dk = (N + 127) // 128 * 128, (D + 15) // 16 * 16
+    least = up(B * Np * Dk * 2) + up(B * Np * 4) + (up(B * M * Dk * 2) if Dk != D else 0)
+    assert km.knn_workspace_bytes(B, M, N, D, k, Qd.dtype) >= least
+    li, ld = torch.empty_like(gi), torch.empty_like(gd)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    km._check(km.lib.kmeans_knn(km._ptr(Qd), km._ptr(Rd), km._dt(Qd), B, M, N, D, k, km._ptr(li),
+                                km._ptr(ld), km._ptr(ws), ws.numel(), km._stream()), "kmeans_knn")
+    torch.cuda.synchronize()
+    if Dk == D:
+        assert torch.equal(li, gi) and torch.equal(ld, gd)
+    else:  # the padded rows' norms are summed in another order on the list kernel
+        assert (ld - gd).abs().max() <= tol.max()
+
+
+def test_knn_duplicate_rows(km):
+    """Equal scores everywhere: the lowest indices, in order, on the scan (more
+    equal candidates than its buffer holds) and on the list kernel's shares."""
+    for M, N in ((3, 70_001), (2_100, 3_000)):
+        R = torch.ones((1, N, 32), dtype=torch.bfloat16, device="cuda")
+        Q = torch.rand((1, M, 32), device="cuda").to(torch.bfloat16)
+        say(f"[knn duplicates] M={M} N={N}")
+        for k in (1, 10, 32):
+            gi, _ = km.kmeans_knn(Q, R, k)
+            assert torch.equal(gi, torch.arange(k, dtype=torch.int32, device="cuda").expand(1, M, k))
+
+
 def test_knn_k1_matches_assignment(km):
     """k = 1 is the assignment with the database rows as centroids (same rows:
     the rows are already in the storage type, so rounding them changes nothing)."""
