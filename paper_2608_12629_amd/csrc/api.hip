@@ -49,6 +49,7 @@ Workspace carve(void* base, int64_t B, int64_t N, int64_t D_user, int64_t K, int
   // flags of the 16-bit streaming assignment (one per block of points)
   const bool streaming16 = dt != DT_F32 && !assign_tiled(dt, D);
   w.wide = (int32_t*)take(streaming16 ? (size_t)(B * w.n_assign_blocks) * 4 : 0);
+  const size_t upd0 = o;  // the update's arrays start here
   // the second packed pass cuts at most RADIX_MAX_R more chunks (one per low digit)
   w.rhist = (int32_t*)take((size_t)(B * RADIX_MAX_R * (w.n_sort_chunks + RADIX_MAX_R)) * 4);
   w.rbin = (int32_t*)take((size_t)B * RADIX_MAX_R * 4);
@@ -66,6 +67,8 @@ Workspace carve(void* base, int64_t B, int64_t N, int64_t D_user, int64_t K, int
   w.n_sk_chunks = (N + SMALLK_CH - 1) / SMALLK_CH;
   w.partial = (float*)take(sk ? (size_t)(B * w.n_sk_chunks * K * D) * 4 : 0);
   w.pcount = (int32_t*)take(sk ? (size_t)(B * w.n_sk_chunks * K) * 4 : 0);
+  w.ascr = (char*)w.rhist;
+  w.ascr_bytes = o - upd0;
   const bool tiled = assign_tiled(dt, D);
   w.keys = (uint64_t*)take(tiled ? (size_t)(B * N + 1) * 8 + TILED_ZERO_BYTES : 0);
   w.xnorm = (float*)take(tiled ? (size_t)(B * N) * 4 : 0);

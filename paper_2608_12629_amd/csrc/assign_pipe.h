@@ -282,7 +282,22 @@ __device__ __forceinline__ void pipe_stage(int st, int next, int nst, float& car
 // shifts each point by its own bound.
 constexpr float PIPE_WIDE_RATIO = 64.f;
 
-// One workgroup's block of PPB points against all centroids.  PPQ = false:
+// A call with fewer blocks of points than the chip holds workgroups shares
+// the centroid stages out: `splits` workgroups per block, `per` stages each.
+// Share s writes, for point i of instance b, keys[(b * splits + s) * N + i] =
+// (score bits << 32 | centroid): scores are negative, so the smallest key is
+// the best score and, among equal ones, the lowest centroid, the choice that
+// one workgroup over all stages makes.  Share 0 also writes the points'
+// squared norms and the block's shift, and merge_block finishes the points.
+struct PipeSplit {
+  int splits, per;
+  uint64_t* keys;  // [B, splits, N]
+  float* xn;       // [B, N]
+  float* q;        // [B, blocks]
+};
+
+// One workgroup's block of PPB points against all centroids (or its share of
+// them: chat4, cinit and nst are the share's).  PPQ = false:
 // the workgroup's shift Q is folded into the stored scores (no cost per
 // tile); a block whose squared norms spread by more than PIPE_WIDE_RATIO is
 // only flagged (wide[blk] = 1) and left alone.  PPQ = true: each point's own
@@ -294,7 +309,8 @@ __device__ __forceinline__ void pipe_block(int blk, const uint4* __restrict__ X,
                                            int32_t* __restrict__ idx, float* __restrict__ min_dist,
                                            double* __restrict__ objpart, int32_t* __restrict__ wide,
                                            char* buf0, char* buf1, float* lds_q, float* lds_qmin,
-                                           double* lds_obj) {
+                                           double* lds_obj, const PipeSplit& sp = PipeSplit{1},
+                                           int share = 0) {
   using L = PipeLayout<CPL>;
   constexpr int RC = L::RC;
   constexpr int PPW = 32 * NSUB;           // points per wave
@@ -373,7 +389,7 @@ __device__ __forceinline__ void pipe_block(int blk, const uint4* __restrict__ X,
                                        __builtin_fminf(lds_qmin[2], lds_qmin[3]));
     // the same value in every thread (from LDS after a barrier): a uniform branch
     const bool spread = wmax > PIPE_WIDE_RATIO * wmin;
-    if (tid == 0) wide[blk] = spread ? 1 : 0;
+    if (tid == 0 && share == 0) wide[blk] = spread ? 1 : 0;
     if (spread) {
       __builtin_amdgcn_s_waitcnt(0);  // the first stage's loads into LDS complete before exit
       return;
@@ -419,6 +435,23 @@ __device__ __forceinline__ void pipe_block(int blk, const uint4* __restrict__ X,
                                           cinit, Q, Qp, tid, prev_code, best, code);
   pipe_epilogue<NSUB, PPQ>(accA, prev_code, best, code, Qp);
 
+  if (!PPQ && sp.splits > 1) {
+    if (share == 0 && tid == 0) sp.q[blk] = Q;
+#pragma unroll
+    for (int p = 0; p < NSUB; ++p) {
+      const uint32_t j = code[p] & 15u;
+      const uint32_t i = (uint32_t)(share * sp.per * L::TCS) + (code[p] >> 4) * 32 + 8 * (j >> 2) +
+                         4 * h + (j & 3);
+      const uint64_t key = (uint64_t)__float_as_uint(best[p]) << 32 | i;
+      const uint64_t ko = __shfl_xor(key, 32);
+      const int pt = pbase + p * 32 + n;
+      if (h == 0 && pt < N) {
+        sp.keys[(size_t)share * N + pt] = key < ko ? key : ko;
+        if (share == 0) sp.xn[pt] = xn[p];
+      }
+    }
+    return;
+  }
   double obj = 0.0;
 #pragma unroll
   for (int p = 0; p < NSUB; ++p) {
@@ -447,14 +480,54 @@ __device__ __forceinline__ void pipe_block(int blk, const uint4* __restrict__ X,
   if (tid == 0) objpart[blk] = ((lds_obj[0] + lds_obj[1]) + lds_obj[2]) + lds_obj[3];
 }
 
+// The points of one block from its shares' keys: the outputs and the objective
+// partial as pipe_block writes them for one share (the same bits, each lane
+// adding the same points).  A lane pair reads the even and the odd shares.
+template <int NSUB>
+__device__ __forceinline__ void pipe_merge_block(int blk, int N, int32_t* __restrict__ idx,
+                                                 float* __restrict__ min_dist,
+                                                 double* __restrict__ objpart, double* lds_obj,
+                                                 const PipeSplit& sp) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 31, h = lane >> 5;
+  const int pbase = (blk * 4 + wave) * 32 * NSUB;
+  const float Q = sp.q[blk];
+  double obj = 0.0;
+#pragma unroll
+  for (int p = 0; p < NSUB; ++p) {
+    const int pt = pbase + p * 32 + n;
+    const bool ok = pt < N;
+    const uint64_t* kp = sp.keys + (ok ? pt : 0);
+    uint64_t key = ~0ull;
+#pragma unroll 8
+    for (int s = h; s < sp.splits; s += 2) key = min(key, kp[(size_t)s * N]);
+    key = min(key, (uint64_t)__shfl_xor(key, 32));
+    if (h == 0 && ok) {
+      const float v = __uint_as_float((uint32_t)(key >> 32)), xn = sp.xn[pt];
+      const bool asg = xn <= __FLT_MAX__ && v > -__FLT_MAX__;
+      const float md = __builtin_fmaxf(__builtin_fmaf(-2.f, v + Q, xn), 0.f);
+      idx[pt] = asg ? (int)(uint32_t)key : -1;
+      min_dist[pt] = asg ? md : __builtin_nanf("");
+      obj += asg ? (double)md : 0.0;
+    }
+  }
+#pragma unroll
+  for (int msk = 1; msk < 64; msk <<= 1) obj += __shfl_xor(obj, msk);
+  if (lane == 0) lds_obj[wave] = obj;
+  __syncthreads();
+  if (tid == 0) objpart[blk] = ((lds_obj[0] + lds_obj[1]) + lds_obj[2]) + lds_obj[3];
+  __syncthreads();
+}
+
 // The assignment of one block of points per workgroup with the workgroup's
-// shift; blocks whose norms spread widely are flagged in `wide` (per
+// shift (blockIdx.z: its share of the centroids); blocks whose norms spread widely are flagged in `wide` (per
 // instance, one int per block) and left to assign_pipe_wide_kernel.
 template <int DT, int CPL, int NSUB>
 __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_kernel(
     const uint4* __restrict__ X, const uint4* __restrict__ chat, const float* __restrict__ cinit,
     int N, int Kp, int32_t* __restrict__ idx, float* __restrict__ min_dist,
-    double* __restrict__ objpart, int32_t* __restrict__ wide) {
+    double* __restrict__ objpart, int32_t* __restrict__ wide, PipeSplit sp) {
   static_assert(DT != DT_F32, "16-bit storage types only");
   static_assert(CPL >= 2, "16-bit rows of 16 elements run on the fp32 kernel");
   using L = PipeLayout<CPL>;
@@ -465,24 +538,30 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_kernel(
   __shared__ __attribute__((aligned(16))) char buf1[L::STAGE];
   __shared__ float lds_q[4], lds_qmin[4];
   __shared__ double lds_obj[4];
-  const int b = blockIdx.y, nblk = gridDim.x;
+  const int b = blockIdx.y, nblk = gridDim.x, share = blockIdx.z;
+  const int st0 = share * sp.per, nst = min(sp.per, Kp / L::TCS - st0);
+  sp.keys += (size_t)b * sp.splits * N;
+  sp.xn += (size_t)b * N;
+  sp.q += (size_t)b * nblk;
   pipe_block<DT, CPL, NSUB, false>(
       blockIdx.x, X + (size_t)b * N * L::RC,
-      reinterpret_cast<const u32x4*>(chat) + (size_t)b * Kp * L::RC, cinit + (size_t)b * Kp, N,
-      Kp / L::TCS, idx + (size_t)b * N, min_dist + (size_t)b * N, objpart + (size_t)b * nblk,
-      wide + (size_t)b * nblk, buf0, buf1, lds_q, lds_qmin, lds_obj);
+      reinterpret_cast<const u32x4*>(chat) + ((size_t)b * Kp + st0 * L::TCS) * L::RC,
+      cinit + (size_t)b * Kp + st0 * L::TCS, N, nst, idx + (size_t)b * N,
+      min_dist + (size_t)b * N, objpart + (size_t)b * nblk, wide + (size_t)b * nblk, buf0, buf1,
+      lds_q, lds_qmin, lds_obj, sp, share);
 }
 
 // The flagged blocks, each point shifted by its own bound.  A fixed grid of
 // workgroups splits the blocks into contiguous ranges; each wave reads 64
 // flags of its range at once (one per lane) and the workgroup assigns the
 // flagged blocks among them, so with no wide block it costs one read of the
-// flags per 64 blocks.
+// flags per 64 blocks.  After a split assignment the same workgroups merge
+// the shares of the blocks that are not flagged.
 template <int DT, int CPL, int NSUB>
 __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_wide_kernel(
     const uint4* __restrict__ X, const uint4* __restrict__ chat, const float* __restrict__ cinit,
     int N, int Kp, int nblk, int32_t* __restrict__ idx, float* __restrict__ min_dist,
-    double* __restrict__ objpart, const int32_t* __restrict__ wide) {
+    double* __restrict__ objpart, const int32_t* __restrict__ wide, PipeSplit sp) {
   using L = PipeLayout<CPL>;
   __shared__ __attribute__((aligned(16))) char buf0[L::STAGE];
   __shared__ __attribute__((aligned(16))) char buf1[L::STAGE];
@@ -491,6 +570,15 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_wide_kernel(
   const int32_t* wb = wide + (size_t)b * nblk;
   const int per = (nblk + gridDim.x - 1) / gridDim.x;
   const int r0 = blockIdx.x * per, r1 = min(r0 + per, nblk);
+  if (sp.splits > 1) {
+    sp.keys += (size_t)b * sp.splits * N;
+    sp.xn += (size_t)b * N;
+    sp.q += (size_t)b * nblk;
+    for (int blk = r0; blk < r1; ++blk)
+      if (wb[blk] == 0)
+        pipe_merge_block<NSUB>(blk, N, idx + (size_t)b * N, min_dist + (size_t)b * N,
+                               objpart + (size_t)b * nblk, lds_obj, sp);
+  }
   for (int g0 = r0; g0 < r1; g0 += 64) {
     const int bl = g0 + (threadIdx.x & 63);
     // every wave reads the same 64 flags, so the mask is the same in all of them
@@ -513,20 +601,59 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_wide_kernel(
 // none is set.
 constexpr int64_t PIPE_WIDE_GRID = 512;
 
+// How a call shares out its nst centroid stages.  The chip holds
+// PIPE_RESIDENT workgroups (two per CU); a workgroup costs about PIPE_FIXED
+// stages besides its own (its points, first stage and tail).  The share count
+// is the one with the least rounds x (fixed + stages per share), and is used
+// only if that saves a quarter and PIPE_MIN_GAIN stages (about 1.3 us each
+// for a workgroup alone on its CU): the merge reads every share's keys.
+// Measured, unshared -> shared (points x D, K): 1,024 x 256, 8,192: 155 -> 24
+// us; 500 x 128, 16,384: 179 -> 21; 60,000 x 64, 4,096: 72 -> 45; 20,000 x
+// 128, 1,024 (8 stages, 6 saved): 20.6 -> 19.4; and, not shared for that
+// reason, 50,000 x 128, 1,024 (4 saved): 21.8 -> 22.8; 1,024 x 256, 256 (3
+// saved): 17.9 -> 19.4.  From 512 blocks on nothing is shared.
+constexpr int64_t PIPE_RESIDENT = 512, PIPE_FIXED = 3, PIPE_MIN_GAIN = 6, PIPE_MAX_SPLITS = 64;
+inline PipeSplit pipe_split(const Workspace& w, int64_t B, int64_t N, int64_t nst) {
+  PipeSplit sp{1, (int)nst, nullptr, nullptr, nullptr};
+  const int64_t blocks = B * w.n_assign_blocks;
+  auto cost = [&](int64_t per) {
+    const int64_t wgs = blocks * ((nst + per - 1) / per);
+    return (wgs + PIPE_RESIDENT - 1) / PIPE_RESIDENT * (PIPE_FIXED + per);
+  };
+  auto align = [](size_t v) { return (v + 255) & ~size_t(255); };
+  auto bytes = [&](int64_t splits) {
+    return align((size_t)(B * splits * N) * 8) + align((size_t)(B * N) * 4) + (size_t)blocks * 4;
+  };
+  int64_t best = nst;
+  for (int64_t s = 2; s <= nst && s <= PIPE_MAX_SPLITS; ++s) {
+    const int64_t per = (nst + s - 1) / s, splits = (nst + per - 1) / per;
+    if (splits <= PIPE_MAX_SPLITS && bytes(splits) <= w.ascr_bytes && cost(per) < cost(best)) best = per;
+  }
+  if (4 * cost(best) > 3 * cost(nst) || cost(best) + PIPE_MIN_GAIN > cost(nst)) return sp;
+  sp.per = (int)best;
+  sp.splits = (int)((nst + best - 1) / best);
+  sp.keys = (uint64_t*)w.ascr;
+  sp.xn = (float*)(w.ascr + align((size_t)(B * sp.splits * N) * 8));
+  sp.q = (float*)((char*)sp.xn + align((size_t)(B * N) * 4));
+  return sp;
+}
+
 template <int DT, int CPL, int NSUB>
 hipError_t launch_pipe(const void* X, const Workspace& w, int64_t B, int64_t N,
                               int32_t* idx, float* min_dist, hipStream_t s) {
-  const dim3 grid((unsigned)w.n_assign_blocks, (unsigned)B), block(ASSIGN_THREADS);
+  const PipeSplit sp = pipe_split(w, B, N, w.Kp / PipeLayout<CPL>::TCS);
+  const dim3 grid((unsigned)w.n_assign_blocks, (unsigned)B, (unsigned)sp.splits);
+  const dim3 block(ASSIGN_THREADS);
   assign_pipe_kernel<DT, CPL, NSUB><<<grid, block, 0, s>>>(
       (const uint4*)X, (const uint4*)w.chat, w.cinit, (int)N, (int)w.Kp, idx, min_dist, w.objpart,
-      w.wide);
+      w.wide, sp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t per = (PIPE_WIDE_GRID + B - 1) / B;  // workgroups per instance
   const int64_t nw = w.n_assign_blocks < per ? w.n_assign_blocks : per;
   assign_pipe_wide_kernel<DT, CPL, NSUB><<<dim3((unsigned)nw, (unsigned)B), block, 0, s>>>(
       (const uint4*)X, (const uint4*)w.chat, w.cinit, (int)N, (int)w.Kp, (int)w.n_assign_blocks,
-      idx, min_dist, w.objpart, w.wide);
+      idx, min_dist, w.objpart, w.wide, sp);
   return hipGetLastError();
 }
 

@@ -154,6 +154,10 @@ struct Workspace {
   int32_t* pcount; // [B,nch,K] per-chunk cluster counts
   uint64_t* keys;  // [B,N] best (score, index) of each point, then TILED_ZERO_BYTES of zeros (tiled assignment only)
   float* xnorm;    // [B,N] squared norms of the points (tiled assignment only)
+  // The update's arrays (rhist .. pcount) are free while an assignment runs:
+  // its scratch, in which a split assignment keeps its shares' results.
+  char* ascr;
+  size_t ascr_bytes;
   void* xpad;      // [B,N,Dk] the points in zero-padded rows of type kdt (only when copied)
   float* cpad;     // [B,K,Dk] the centroids in zero-padded rows (only when copied)
   int64_t Dk;      // the row width the kernels run at (kernel_dim)

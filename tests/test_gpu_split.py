@@ -1,0 +1,60 @@
+"""Calls with few points, whose centroids are shared out among workgroups: the
+same points among so many instances that nothing is shared give the same bits."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DT = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}
+
+
+@pytest.fixture(scope="module")
+def km():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    from paper_2608_12629_amd import kmeans
+    return kmeans
+
+
+# one point; a block and one more; 64-row stages (D = 256) with a short last
+# share; four point tiles a wave (D <= 64); widths that are padded; tie-heavy
+# duplicates are in every case (the second half of C
+# repeats the first)
+@pytest.mark.parametrize("N,D,K,dt,B", [
+    (1, 128, 2050, "bf16", 513), (257, 128, 4100, "f16", 260), (130, 256, 3001, "bf16", 260),
+    (513, 32, 5000, "f16", 260), (100, 100, 2500, "bf16", 520), (65, 200, 2222, "f16", 520),
+])
+def test_shared_centroids_same_bits(km, N, D, K, dt, B):
+    g = torch.Generator().manual_seed(N + D + K)
+    X = torch.randn((1, N, D), generator=g)
+    if N > 4:
+        X[0, 1] = float("nan")
+        X[0, 2, 0] = float("inf")
+    if N > 256:
+        X[0, 256:] *= 100.0  # a block whose norms spread widely, and its own point shifts
+        X[0, 3] *= 100.0
+    C = torch.randn((1, K, D), generator=g)
+    C[0, K // 2:] = C[0, :K - K // 2].clone()
+    C[0, 7] = float("nan")
+    X, C = X.to(DT[dt]).cuda(), C.cuda()
+    idx, md = km.kmeans_assign(X, C)
+    Xb, Cb = X.expand(B, N, D).contiguous(), C.expand(B, K, D).contiguous()
+    idx_b, md_b = km.kmeans_assign(Xb, Cb)
+    assert torch.equal(idx_b, idx.expand(B, N))
+    assert torch.equal(md_b.view(torch.int32), md.view(torch.int32).expand(B, N))
+    ok = idx[0] >= 0
+    assert int((~ok).sum()) == (2 if N > 4 else 0)
+    d = (X[0].double()[ok][:, None] - C[0].to(DT[dt]).double()[None].nan_to_num(1e4)).square().sum(-1)
+    best = d.min(1).values
+    got = d.gather(1, idx[0][ok].long()[:, None])[:, 0]
+    xn = X[0].double()[ok].square().sum(-1)
+    assert bool((got - best <= 1e-3 * xn).all())
+    # objective and state of a Lloyd step, one instance against many
+    J = torch.empty((1, 1), dtype=torch.float64, device="cuda")
+    Jb = torch.empty((B, 1), dtype=torch.float64, device="cuda")
+    C1, Cb1 = C.clone(), Cb.clone()
+    km.kmeans_lloyd(X, C1, 1, objective=J)
+    km.kmeans_lloyd(Xb, Cb1, 1, objective=Jb)
+    assert torch.equal(Jb, J.expand(B, 1))
+    assert torch.equal(Cb1.view(torch.int32), C1.view(torch.int32).expand(B, K, D))
