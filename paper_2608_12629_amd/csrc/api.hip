@@ -193,10 +193,16 @@ int kmeans_assign(const void* X, int xdtype, const float* C, int64_t B, int64_t 
   if ((rc = check_device())) return rc;
   hipStream_t s = (hipStream_t)stream;
   const Workspace w = carve(ws, B, N, D, K, xdtype);
-  KernelArgs a;
-  if ((rc = hip_status(pad_inputs(X, C, xdtype, w, B, N, D, K, &a, s)))) return rc;
-  if ((rc = hip_status(launch_prep(a.C, w.kdt, B, K, w.Kp, w.Dk, w.chat, w.cinit, s)))) return rc;
-  return hip_status(launch_assign(a.X, w.kdt, w, B, N, w.Dk, K, idx, min_dist, s));
+  // The centroids are read in place, and the points too by the kernels that
+  // take rows of any width.
+  KernelArgs a{X, nullptr};
+  int64_t Din = D;
+  if (w.kdt != xdtype || !assign_in_place(w.kdt, w.Dk, K)) {
+    if ((rc = hip_status(pad_inputs(X, nullptr, xdtype, w, B, N, D, K, &a, s)))) return rc;
+    Din = w.Dk;
+  }
+  if ((rc = hip_status(launch_prep(C, w.kdt, B, K, w.Kp, D, w.Dk, w.chat, w.cinit, s)))) return rc;
+  return hip_status(launch_assign(a.X, w.kdt, w, B, N, Din, w.Dk, K, idx, min_dist, s));
 }
 
 int kmeans_update(const void* X, int xdtype, const int32_t* idx, const float* C_prev, int64_t B,
@@ -253,14 +259,14 @@ int kmeans_lloyd(const void* X, int xdtype, float* C, int64_t B, int64_t N, int6
   nx.nparts = sums_ok(kdt, Dk, K) ? w.n_sk_chunks : w.n_assign_blocks;
   nx.iters = iters;
   nx.objective = objective;
-  if ((rc = hip_status(launch_prep(a.C, kdt, B, K, w.Kp, Dk, w.chat, w.cinit, s)))) return rc;
+  if ((rc = hip_status(launch_prep(a.C, kdt, B, K, w.Kp, Dk, Dk, w.chat, w.cinit, s)))) return rc;
   for (int t = 0; t < iters; ++t) {
     nx.t = t;
     if (t + 1 == iters) nx.chat = nullptr;  // no next iteration
     if (fused)
       rc = hip_status(launch_sums(a.X, kdt, w, B, N, Dk, K, SUMS_FUSED, idx, min_dist, s));
     else
-      rc = hip_status(launch_assign(a.X, kdt, w, B, N, Dk, K, idx, min_dist, s));
+      rc = hip_status(launch_assign(a.X, kdt, w, B, N, Dk, Dk, K, idx, min_dist, s));
     if (rc) return rc;
     if (fused)
       rc = hip_status(launch_combine(w, w.n_sk_chunks, a.C, B, K, Dk, a.C, counts, nx, s));

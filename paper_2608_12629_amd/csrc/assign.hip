@@ -30,7 +30,8 @@ namespace fkm {
 // Rows K..Kp-1 of each instance are padding: zero, with cinit = -FLT_MAX.
 template <int DT>
 __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ C, int64_t B, int K,
-                                                   int Kp, int D, void* __restrict__ chat,
+                                                   int Kp, int Dc, int D,
+                                                   void* __restrict__ chat,
                                                    float* __restrict__ cinit) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -38,7 +39,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ C, 
   const int64_t b = row / Kp;
   const int k = (int)(row % Kp);
   const bool pad = k >= K;
-  prep_row<DT>(C + (b * K + (pad ? 0 : k)) * D, pad, D, lane,
+  prep_row<DT>(C + (b * K + (pad ? 0 : k)) * Dc, pad, Dc, D, lane,
                (char*)chat + row * D * (DT == DT_F32 ? 4 : 2), cinit + row);
 }
 
@@ -191,15 +192,18 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_resident_kernel(
 
 
 // ---------------------------------------------------------------------------
-hipError_t launch_prep(const float* C, int dt, int64_t B, int64_t K, int64_t Kp, int64_t D,
-                       void* chat, float* cinit, hipStream_t s) {
+hipError_t launch_prep(const float* C, int dt, int64_t B, int64_t K, int64_t Kp, int64_t Dc,
+                       int64_t D, void* chat, float* cinit, hipStream_t s) {
   const dim3 grid((unsigned)((B * Kp + 3) / 4)), block(256);
   if (dt == DT_BF16)
-    prep_kernel<DT_BF16><<<grid, block, 0, s>>>(C, B, (int)K, (int)Kp, (int)D, chat, cinit);
+    prep_kernel<DT_BF16><<<grid, block, 0, s>>>(C, B, (int)K, (int)Kp, (int)Dc, (int)D, chat,
+                                                  cinit);
   else if (dt == DT_F16)
-    prep_kernel<DT_F16><<<grid, block, 0, s>>>(C, B, (int)K, (int)Kp, (int)D, chat, cinit);
+    prep_kernel<DT_F16><<<grid, block, 0, s>>>(C, B, (int)K, (int)Kp, (int)Dc, (int)D, chat,
+                                                  cinit);
   else
-    prep_kernel<DT_F32><<<grid, block, 0, s>>>(C, B, (int)K, (int)Kp, (int)D, chat, cinit);
+    prep_kernel<DT_F32><<<grid, block, 0, s>>>(C, B, (int)K, (int)Kp, (int)Dc, (int)D, chat,
+                                                  cinit);
   return hipGetLastError();
 }
 
@@ -247,13 +251,15 @@ static hipError_t launch_resident_dt(const void* X, const Workspace& w, int64_t 
 }
 
 hipError_t launch_assign(const void* X, int dt, const Workspace& w, int64_t B, int64_t N,
-                         int64_t D, int64_t K, int32_t* idx, float* min_dist, hipStream_t s) {
+                         int64_t Din, int64_t D, int64_t K, int32_t* idx, float* min_dist,
+                         hipStream_t s) {
+  if (Din != D && !assign_in_place(dt, D, K)) return hipErrorInvalidValue;
   if (assign_tiled(dt, D)) return launch_assign_tiled(X, dt, w, B, N, D, idx, min_dist, s);
   if (!assign_resident_ok(dt, D)) return hipErrorInvalidValue;
   // small K: the kernel of the fused step, without the sums (the same bits)
   if (sums_ok(dt, D, K)) return launch_sums(X, dt, w, B, N, D, K, SUMS_ASSIGN, idx, min_dist, s);
-  if (dt == DT_BF16) return launch_pipe_bf16(X, w, B, N, D, idx, min_dist, s);
-  if (dt == DT_F16) return launch_pipe_f16(X, w, B, N, D, idx, min_dist, s);
+  if (dt == DT_BF16) return launch_pipe_bf16(X, w, B, N, Din, D, idx, min_dist, s);
+  if (dt == DT_F16) return launch_pipe_f16(X, w, B, N, Din, D, idx, min_dist, s);
   return launch_resident_dt<DT_F32>(X, w, B, N, D, K, idx, min_dist, s);
 }
 

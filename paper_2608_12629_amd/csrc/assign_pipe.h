@@ -166,6 +166,28 @@ __device__ __forceinline__ void pipe_issue_rows(const uint4* __restrict__ X, int
   }
 }
 
+// This lane's fragments of a row of D elements (16 CPL - 16 < D < 16 CPL) read
+// in place, zeros past its end.  Rows of any D start at any 2-byte boundary;
+// every 16-byte load stays inside its row: one that would pass the end loads
+// the last 8 elements (D >= 17) and shifts.  Only the last two chunks of the
+// upper half can.
+template <int CPL>
+__device__ __forceinline__ void ragged_row(const uint16_t* row, int D, int h, uint4 (&x)[CPL]) {
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) {
+    const int e0 = (h * CPL + c) * 8;
+    if (c < CPL - 2) {
+      __builtin_memcpy(&x[c], row + e0, 16);
+    } else {
+      const int e = min(e0, D - 8), sh = 16 * (e0 - e);  // bits
+      unsigned __int128 v;
+      __builtin_memcpy(&v, row + e, 16);
+      v = sh < 128 ? v >> sh : 0;
+      x[c] = __builtin_bit_cast(uint4, v);
+    }
+  }
+}
+
 // The MFMAs of one 32-centroid tile into acc; each chain starts from the scores' init.
 template <int DT, int TILE, int CPL, int NSUB, int LOADS>
 __device__ __forceinline__ void pipe_mfma_tile(f32x16 (&acc)[NSUB], const uint4 (&xr)[NSUB][CPL],
@@ -302,9 +324,9 @@ struct PipeSplit {
 // tile); a block whose squared norms spread by more than PIPE_WIDE_RATIO is
 // only flagged (wide[blk] = 1) and left alone.  PPQ = true: each point's own
 // shift, subtracted in the epilogue (16 subtractions per tile and point tile).
-template <int DT, int CPL, int NSUB, bool PPQ>
+template <int DT, int CPL, int NSUB, bool PPQ, bool RAGGED>
 __device__ __forceinline__ void pipe_block(int blk, const uint4* __restrict__ X,
-                                           const u32x4* __restrict__ chat4,
+                                           int Din, const u32x4* __restrict__ chat4,
                                            const float* __restrict__ cinit, int N, int nst,
                                            int32_t* __restrict__ idx, float* __restrict__ min_dist,
                                            double* __restrict__ objpart, int32_t* __restrict__ wide,
@@ -330,9 +352,20 @@ __device__ __forceinline__ void pipe_block(int blk, const uint4* __restrict__ X,
   // direct fragments (16 bytes of each of 32 rows per instruction) cost about
   // as long again from cache as from memory: the loads' own cost, not the
   // latency.  The first centroid stage then follows into buf0.
+  // Rows narrower than the kernel's (with RAGGED, when Din says so) are loaded
+  // in place as direct fragments.  200,003 rows of 100 fp16 elements, K =
+  // 1,003: 102 us with padded copies of the points (27) and centroids (10),
+  // 53 now; 1,000,000 x 100, K = 256: 255 -> 81.
   constexpr bool XLDS = PPB == 2 * L::TCS;
   float n0;
-  if constexpr (XLDS) {
+  if (RAGGED && Din != 8 * RC) {
+    n0 = pipe_issue_stage<CPL, LOADS>(chat4, cinit, 0, tid, o, buf0);
+#pragma unroll
+    for (int p = 0; p < NSUB; ++p) {
+      const int pt = min(pbase + p * 32 + n, N - 1);
+      ragged_row<CPL>(reinterpret_cast<const uint16_t*>(X) + (size_t)pt * Din, Din, h, xr[p]);
+    }
+  } else if constexpr (XLDS) {
     pipe_issue_rows<CPL, LOADS>(X, blk * PPB, N, tid, buf0);
     pipe_issue_rows<CPL, LOADS>(X, blk * PPB + L::TCS, N, tid, buf1);
     __builtin_amdgcn_s_waitcnt(0);
@@ -520,13 +553,19 @@ __device__ __forceinline__ void pipe_merge_block(int blk, int N, int32_t* __rest
   __syncthreads();
 }
 
+// An instance's points, `elems` 16-bit elements from X (only in-place rows
+// start off a 16-byte boundary).
+__device__ __forceinline__ const uint4* pipe_instance(const uint4* X, size_t elems) {
+  return reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(X) + elems);
+}
+
 // The assignment of one block of points per workgroup with the workgroup's
 // shift (blockIdx.z: its share of the centroids); blocks whose norms spread widely are flagged in `wide` (per
 // instance, one int per block) and left to assign_pipe_wide_kernel.
-template <int DT, int CPL, int NSUB>
+template <int DT, int CPL, int NSUB, bool RAGGED>
 __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_kernel(
-    const uint4* __restrict__ X, const uint4* __restrict__ chat, const float* __restrict__ cinit,
-    int N, int Kp, int32_t* __restrict__ idx, float* __restrict__ min_dist,
+    const uint4* __restrict__ X, int Din, const uint4* __restrict__ chat,
+    const float* __restrict__ cinit, int N, int Kp, int32_t* __restrict__ idx, float* __restrict__ min_dist,
     double* __restrict__ objpart, int32_t* __restrict__ wide, PipeSplit sp) {
   static_assert(DT != DT_F32, "16-bit storage types only");
   static_assert(CPL >= 2, "16-bit rows of 16 elements run on the fp32 kernel");
@@ -543,8 +582,8 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_kernel(
   sp.keys += (size_t)b * sp.splits * N;
   sp.xn += (size_t)b * N;
   sp.q += (size_t)b * nblk;
-  pipe_block<DT, CPL, NSUB, false>(
-      blockIdx.x, X + (size_t)b * N * L::RC,
+  pipe_block<DT, CPL, NSUB, false, RAGGED>(
+      blockIdx.x, pipe_instance(X, (size_t)b * N * Din), Din,
       reinterpret_cast<const u32x4*>(chat) + ((size_t)b * Kp + st0 * L::TCS) * L::RC,
       cinit + (size_t)b * Kp + st0 * L::TCS, N, nst, idx + (size_t)b * N,
       min_dist + (size_t)b * N, objpart + (size_t)b * nblk, wide + (size_t)b * nblk, buf0, buf1,
@@ -559,8 +598,8 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_kernel(
 // the shares of the blocks that are not flagged.
 template <int DT, int CPL, int NSUB>
 __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_wide_kernel(
-    const uint4* __restrict__ X, const uint4* __restrict__ chat, const float* __restrict__ cinit,
-    int N, int Kp, int nblk, int32_t* __restrict__ idx, float* __restrict__ min_dist,
+    const uint4* __restrict__ X, int Din, const uint4* __restrict__ chat,
+    const float* __restrict__ cinit, int N, int Kp, int nblk, int32_t* __restrict__ idx, float* __restrict__ min_dist,
     double* __restrict__ objpart, const int32_t* __restrict__ wide, PipeSplit sp) {
   using L = PipeLayout<CPL>;
   __shared__ __attribute__((aligned(16))) char buf0[L::STAGE];
@@ -586,8 +625,8 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_pipe_wide_kernel(
     while (m != 0) {
       const int blk = g0 + __builtin_ctzll(m);
       m &= m - 1;
-      pipe_block<DT, CPL, NSUB, true>(
-          blk, X + (size_t)b * N * L::RC,
+      pipe_block<DT, CPL, NSUB, true, true>(
+          blk, pipe_instance(X, (size_t)b * N * Din), Din,
           reinterpret_cast<const u32x4*>(chat) + (size_t)b * Kp * L::RC, cinit + (size_t)b * Kp, N,
           Kp / L::TCS, idx + (size_t)b * N, min_dist + (size_t)b * N, objpart + (size_t)b * nblk,
           nullptr, buf0, buf1, nullptr, nullptr, lds_obj);
@@ -639,20 +678,23 @@ inline PipeSplit pipe_split(const Workspace& w, int64_t B, int64_t N, int64_t ns
 }
 
 template <int DT, int CPL, int NSUB>
-hipError_t launch_pipe(const void* X, const Workspace& w, int64_t B, int64_t N,
-                              int32_t* idx, float* min_dist, hipStream_t s) {
+hipError_t launch_pipe(const void* X, const Workspace& w, int64_t B, int64_t N, int64_t Din,
+                       int32_t* idx, float* min_dist, hipStream_t s) {
   const PipeSplit sp = pipe_split(w, B, N, w.Kp / PipeLayout<CPL>::TCS);
   const dim3 grid((unsigned)w.n_assign_blocks, (unsigned)B, (unsigned)sp.splits);
   const dim3 block(ASSIGN_THREADS);
-  assign_pipe_kernel<DT, CPL, NSUB><<<grid, block, 0, s>>>(
-      (const uint4*)X, (const uint4*)w.chat, w.cinit, (int)N, (int)w.Kp, idx, min_dist, w.objpart,
-      w.wide, sp);
+  // two kernels: with both ways of loading the points in one, the kernel for
+  // rows of whole chunks took 8 more registers (256 at D = 128)
+  (Din == 16 * CPL ? assign_pipe_kernel<DT, CPL, NSUB, false>
+                   : assign_pipe_kernel<DT, CPL, NSUB, true>)<<<grid, block, 0, s>>>(
+      (const uint4*)X, (int)Din, (const uint4*)w.chat, w.cinit, (int)N, (int)w.Kp, idx, min_dist,
+      w.objpart, w.wide, sp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t per = (PIPE_WIDE_GRID + B - 1) / B;  // workgroups per instance
   const int64_t nw = w.n_assign_blocks < per ? w.n_assign_blocks : per;
   assign_pipe_wide_kernel<DT, CPL, NSUB><<<dim3((unsigned)nw, (unsigned)B), block, 0, s>>>(
-      (const uint4*)X, (const uint4*)w.chat, w.cinit, (int)N, (int)w.Kp, (int)w.n_assign_blocks,
+      (const uint4*)X, (int)Din, (const uint4*)w.chat, w.cinit, (int)N, (int)w.Kp, (int)w.n_assign_blocks,
       idx, min_dist, w.objpart, w.wide, sp);
   return hipGetLastError();
 }
@@ -660,25 +702,25 @@ hipError_t launch_pipe(const void* X, const Workspace& w, int64_t B, int64_t N,
 // CPL = D / 16 chunks per lane (2 .. 16: 16-bit rows of 16 run as fp32);
 // NSUB must agree with assign_nsub16(D).
 template <int DT>
-hipError_t launch_pipe_dt(const void* X, const Workspace& w, int64_t B, int64_t N,
-                                 int64_t D, int32_t* idx, float* min_dist, hipStream_t s) {
+hipError_t launch_pipe_dt(const void* X, const Workspace& w, int64_t B, int64_t N, int64_t Din,
+                          int64_t D, int32_t* idx, float* min_dist, hipStream_t s) {
   if (D % 16 != 0) return hipErrorInvalidValue;
   switch (D / 16) {
-    case 2: return launch_pipe<DT, 2, 4>(X, w, B, N, idx, min_dist, s);
-    case 3: return launch_pipe<DT, 3, 4>(X, w, B, N, idx, min_dist, s);
-    case 4: return launch_pipe<DT, 4, 4>(X, w, B, N, idx, min_dist, s);
-    case 5: return launch_pipe<DT, 5, 2>(X, w, B, N, idx, min_dist, s);
-    case 6: return launch_pipe<DT, 6, 2>(X, w, B, N, idx, min_dist, s);
-    case 7: return launch_pipe<DT, 7, 2>(X, w, B, N, idx, min_dist, s);
-    case 8: return launch_pipe<DT, 8, 2>(X, w, B, N, idx, min_dist, s);
-    case 9: return launch_pipe<DT, 9, 1>(X, w, B, N, idx, min_dist, s);
-    case 10: return launch_pipe<DT, 10, 1>(X, w, B, N, idx, min_dist, s);
-    case 11: return launch_pipe<DT, 11, 1>(X, w, B, N, idx, min_dist, s);
-    case 12: return launch_pipe<DT, 12, 1>(X, w, B, N, idx, min_dist, s);
-    case 13: return launch_pipe<DT, 13, 1>(X, w, B, N, idx, min_dist, s);
-    case 14: return launch_pipe<DT, 14, 1>(X, w, B, N, idx, min_dist, s);
-    case 15: return launch_pipe<DT, 15, 1>(X, w, B, N, idx, min_dist, s);
-    case 16: return launch_pipe<DT, 16, 1>(X, w, B, N, idx, min_dist, s);
+    case 2: return launch_pipe<DT, 2, 4>(X, w, B, N, Din, idx, min_dist, s);
+    case 3: return launch_pipe<DT, 3, 4>(X, w, B, N, Din, idx, min_dist, s);
+    case 4: return launch_pipe<DT, 4, 4>(X, w, B, N, Din, idx, min_dist, s);
+    case 5: return launch_pipe<DT, 5, 2>(X, w, B, N, Din, idx, min_dist, s);
+    case 6: return launch_pipe<DT, 6, 2>(X, w, B, N, Din, idx, min_dist, s);
+    case 7: return launch_pipe<DT, 7, 2>(X, w, B, N, Din, idx, min_dist, s);
+    case 8: return launch_pipe<DT, 8, 2>(X, w, B, N, Din, idx, min_dist, s);
+    case 9: return launch_pipe<DT, 9, 1>(X, w, B, N, Din, idx, min_dist, s);
+    case 10: return launch_pipe<DT, 10, 1>(X, w, B, N, Din, idx, min_dist, s);
+    case 11: return launch_pipe<DT, 11, 1>(X, w, B, N, Din, idx, min_dist, s);
+    case 12: return launch_pipe<DT, 12, 1>(X, w, B, N, Din, idx, min_dist, s);
+    case 13: return launch_pipe<DT, 13, 1>(X, w, B, N, Din, idx, min_dist, s);
+    case 14: return launch_pipe<DT, 14, 1>(X, w, B, N, Din, idx, min_dist, s);
+    case 15: return launch_pipe<DT, 15, 1>(X, w, B, N, Din, idx, min_dist, s);
+    case 16: return launch_pipe<DT, 16, 1>(X, w, B, N, Din, idx, min_dist, s);
     default: return hipErrorInvalidValue;
   }
 }

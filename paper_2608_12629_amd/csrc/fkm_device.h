@@ -76,13 +76,15 @@ __device__ inline float tree_sumsq(const uint4 (&a)[CPL]) {
 // whose |c^|^2 is not finite (a NaN or infinite coordinate) is written as a
 // padding row, so it is never chosen and the kernels' scores stay finite or
 // NaN-free (an infinite score with position bits in its low mantissa would
-// become a signalling NaN in the arg-max tree).
+// become a signalling NaN in the arg-max tree).  c holds Dc <= D elements;
+// the rest of the row is zeros.
 template <int DT>
-__device__ inline void prep_row(const float* c, bool pad, int D, int lane, void* out,
+__device__ inline void prep_row(const float* c, bool pad, int Dc, int D, int lane, void* out,
                                 float* cinit) {
+  auto at = [&](int d) -> float { return d < Dc ? c[d] : 0.f; };
   auto rounded = [&](int d) -> float {
-    if constexpr (DT == DT_F32) return c[d];
-    else return Elem<DT>::widen(Elem<DT>::narrow(c[d]));
+    if constexpr (DT == DT_F32) return at(d);
+    else return Elem<DT>::widen(Elem<DT>::narrow(at(d)));
   };
   float ss = 0.f;
   if (!pad) {
@@ -96,10 +98,10 @@ __device__ inline void prep_row(const float* c, bool pad, int D, int lane, void*
   const bool zero = pad || !(ss <= __FLT_MAX__);  // the same in every lane
   if constexpr (DT == DT_F32) {
     float* o = (float*)out;
-    for (int d = lane; d < D; d += 64) o[d] = zero ? 0.f : c[d];
+    for (int d = lane; d < D; d += 64) o[d] = zero ? 0.f : at(d);
   } else {
     uint16_t* o = (uint16_t*)out;
-    for (int d = lane; d < D; d += 64) o[d] = zero ? (uint16_t)0 : Elem<DT>::narrow(c[d]);
+    for (int d = lane; d < D; d += 64) o[d] = zero ? (uint16_t)0 : Elem<DT>::narrow(at(d));
   }
   if (lane == 0) *cinit = zero ? -0x1.fffffep127f : -0.5f * ss;
 }

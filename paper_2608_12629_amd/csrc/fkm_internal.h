@@ -73,6 +73,11 @@ inline int64_t sums_tiles(int64_t D, int64_t K) {
 inline bool sums_ok(int dt, int64_t D, int64_t K) {
   return dt != DT_F32 && D % 16 == 0 && D >= 32 && D <= 96 && K <= 256 && sums_tiles(D, K) <= 8;
 }
+// The streaming 16-bit assignment reads rows of any width in place (it loads
+// each point once, straight into registers); the others read padded copies.
+inline bool assign_in_place(int dt, int64_t D, int64_t K) {
+  return dt != DT_F32 && D <= 256 && !sums_ok(dt, D, K);
+}
 inline bool fused_ok(int dt, int64_t D, int64_t K) { return sums_ok(dt, D, K) && sums_tiles(D, K) <= 4; }
 // KNN search: k nearest database rows per query, k <= KNN_MAX_K.
 constexpr int KNN_MAX_K = 32;
@@ -184,14 +189,17 @@ struct NextStep {
 };
 
 // ---- launchers (return hipSuccess or the launch error) ----------------------
-hipError_t launch_prep(const float* C, int dt, int64_t B, int64_t K, int64_t Kp, int64_t D,
-                       void* chat, float* cinit, hipStream_t s);
+// (C [B,K,Dc] into rows of D >= Dc; X [B,N,Din] into rows of D in registers:
+// Din < D where assign_in_place holds)
+hipError_t launch_prep(const float* C, int dt, int64_t B, int64_t K, int64_t Kp, int64_t Dc,
+                       int64_t D, void* chat, float* cinit, hipStream_t s);
 hipError_t launch_assign(const void* X, int dt, const Workspace& w, int64_t B, int64_t N,
-                         int64_t D, int64_t K, int32_t* idx, float* min_dist, hipStream_t s);
-hipError_t launch_pipe_bf16(const void* X, const Workspace& w, int64_t B, int64_t N, int64_t D,
-                           int32_t* idx, float* min_dist, hipStream_t s);
-hipError_t launch_pipe_f16(const void* X, const Workspace& w, int64_t B, int64_t N, int64_t D,
-                          int32_t* idx, float* min_dist, hipStream_t s);
+                         int64_t Din, int64_t D, int64_t K, int32_t* idx, float* min_dist,
+                         hipStream_t s);
+hipError_t launch_pipe_bf16(const void* X, const Workspace& w, int64_t B, int64_t N, int64_t Din,
+                           int64_t D, int32_t* idx, float* min_dist, hipStream_t s);
+hipError_t launch_pipe_f16(const void* X, const Workspace& w, int64_t B, int64_t N, int64_t Din,
+                          int64_t D, int32_t* idx, float* min_dist, hipStream_t s);
 // sums_ok shapes, by mode: SUMS_ASSIGN the assignment (idx, min_dist and
 // objective partials, one per SMALLK_CH points), SUMS_FUSED that plus the
 // per-chunk partial sums and counts, SUMS_ONLY the partials of the given idx.

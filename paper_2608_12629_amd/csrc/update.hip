@@ -525,9 +525,9 @@ __device__ inline void next_step_tail(const NextStep& nx, const float* row, int6
   if (nx.chat && has_row && tt < 64) {  // the first wave of the cluster's thread group
     const int64_t r = b * nx.Kp + k;
     void* out = (char*)nx.chat + r * D * dt_bytes(nx.dt);
-    if (nx.dt == DT_BF16) prep_row<DT_BF16>(row, false, D, tt, out, nx.cinit + r);
-    else if (nx.dt == DT_F16) prep_row<DT_F16>(row, false, D, tt, out, nx.cinit + r);
-    else prep_row<DT_F32>(row, false, D, tt, out, nx.cinit + r);
+    if (nx.dt == DT_BF16) prep_row<DT_BF16>(row, false, D, D, tt, out, nx.cinit + r);
+    else if (nx.dt == DT_F16) prep_row<DT_F16>(row, false, D, D, tt, out, nx.cinit + r);
+    else prep_row<DT_F32>(row, false, D, D, tt, out, nx.cinit + r);
   }
   if (nx.objective && obj_block) {
     // a thread adds its partials (every 256th) in index order; the loads go
