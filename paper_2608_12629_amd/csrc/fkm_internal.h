@@ -37,6 +37,7 @@ inline int64_t kpad(int64_t K) { return (K + ASSIGN_KPAD - 1) / ASSIGN_KPAD * AS
 constexpr int RADIX_CHUNK = 4096;
 constexpr int RADIX_MAX_BITS = 8;
 constexpr int RADIX_MAX_R = 1 << RADIX_MAX_BITS;
+constexpr int RADIX_ONE_R = 1024;  // most bins of a sort in one pass
 constexpr int64_t RED_MIN = 128, RED_MAX = 2048, RED_WAVES = 4096;
 inline int64_t red_slice(int64_t B, int64_t N) {
   int64_t r = RED_MIN;

@@ -14,6 +14,7 @@
 //   4. finalize   per cluster, the sum (or its partials, in chunk order) over
 //                 the count; an empty cluster keeps its previous centroid.
 #include <algorithm>
+#include <type_traits>
 
 #include "fkm_device.h"
 
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(256) void radix_hist_kernel(const int32_t* __restri
                                                          int32_t* __restrict__ H, int pb,
                                                          const int32_t* __restrict__ T1,
                                                          int lo_bits) {
-  __shared__ int cnt[RADIX_MAX_R];
+  __shared__ int cnt[RADIX_ONE_R];
   __shared__ int wsum[8], sel[5];
   const int b = blockIdx.y, ch = blockIdx.x, t = threadIdx.x;
   int e0, e1, lo;
@@ -147,10 +148,10 @@ __global__ __launch_bounds__(256) void radix_hist_kernel(const int32_t* __restri
 }
 
 // Per bin (one workgroup each): exclusive scan of the bin's chunk counts in
-// place, and the bin total into T[b][bin].  Bin starts are the exclusive scan
-// of T, done by each scatter workgroup on its own (R <= 256 values).
+// place, and the bin total into T[b][bin] (tstride bins per instance).  Bin starts are the exclusive scan
+// of T, done by each scatter workgroup on its own.
 __global__ __launch_bounds__(256) void radix_scan_kernel(int32_t* __restrict__ H, int R, int nch,
-                                                         int32_t* __restrict__ T) {
+                                                         int tstride, int32_t* __restrict__ T) {
   __shared__ int wsum[4];
   const int r = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
   int32_t* h = H + ((size_t)b * R + r) * nch;
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(256) void radix_scan_kernel(int32_t* __restrict__ H
       run += v[u];
     }
   }
-  if (t == 0) T[(size_t)b * RADIX_MAX_R + r] = bin_total;
+  if (t == 0) T[(size_t)b * tstride + r] = bin_total;
 }
 
 // MODE 0: (key, value) arrays in and out (values default to the entry index).
@@ -183,6 +184,9 @@ __global__ __launch_bounds__(256) void radix_scan_kernel(int32_t* __restrict__ H
 //   (key >> lo_bits) << pb | point id.
 // MODE 2 (second pass, packed): packed words in, in the chunks of lo_chunk,
 //   so a chunk's low digit is known and restores each key; point ids out.
+// MODE 3 (the only pass, the whole key one digit of up to 10 bits): keys in,
+//   point ids out; the bins are the clusters, so the bin starts are the
+//   cluster offsets and the first chunk's workgroup writes them.
 //
 // Ranking.  Each wave takes a quarter of the chunk in entry order, in steps
 // of 64 entries.  In a step the lanes holding one digit find each other with
@@ -205,10 +209,14 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(
     const int32_t* __restrict__ T1, int32_t* __restrict__ off) {
   constexpr int STEPS = RADIX_CHUNK / 256;  // 64-entry steps per wave
   constexpr int R = 1 << DBITS;
-  static_assert(R <= 256, "one thread per digit in the scans");
+  static_assert(MODE == 3 || R <= 256, "one thread per digit in the scans");
+  constexpr int BPT = R <= 256 ? 1 : R / 256;  // digits per thread in the scans
+  constexpr int TSTR = MODE == 3 ? R : RADIX_MAX_R;
+  constexpr int RSH = DBITS <= 8 ? 8 : 10;      // the rank's place in `meta`
+  using Digit = std::conditional_t<R <= 256, uint8_t, uint16_t>;
   __shared__ int sval[RADIX_CHUNK];                 // output words in sorted order
   __shared__ int skey[MODE == 0 ? RADIX_CHUNK : 1];  // keys too when they are written out
-  __shared__ uint8_t sdg[RADIX_CHUNK];              // digit of each sorted entry
+  __shared__ Digit sdg[RADIX_CHUNK];                // digit of each sorted entry
   __shared__ int cnt[4][R];                          // per-wave digit counts, then starts
   __shared__ int gdelta[R];
   __shared__ int wsum[4][4], sel[5];
@@ -238,15 +246,33 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(
     if constexpr (MODE == 0) v[s] = in ? (vb ? vb[i] : i) : 0;
   }
   // this bin's total over all chunks and its count before this chunk
-  const int tbin = t < R ? T[(size_t)b * RADIX_MAX_R + t] : 0;
-  const int hrun = t < R ? H[((size_t)b * R + t) * nch + ch] : 0;
-  if (t < R) {
+  int tbin[BPT], hrun[BPT], tsum = 0;
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) cnt[ww][t] = 0;
+  for (int i = 0; i < BPT; ++i) {
+    const int r = t * BPT + i;
+    tbin[i] = r < R ? T[(size_t)b * TSTR + r] : 0;
+    hrun[i] = r < R ? H[((size_t)b * R + r) * nch + ch] : 0;
+    tsum += tbin[i];
+    if (r < R) {
+#pragma unroll
+      for (int ww = 0; ww < 4; ++ww) cnt[ww][r] = 0;
+    }
   }
   // bin starts: exclusive scan of the bin totals (its barrier also orders the zeroing)
   int n_valid;
-  const int bstart = block_scan256(tbin, wsum[0], n_valid);
+  int bstart[BPT];
+  bstart[0] = block_scan256(tsum, wsum[0], n_valid);
+#pragma unroll
+  for (int i = 1; i < BPT; ++i) bstart[i] = bstart[i - 1] + tbin[i - 1];
+  if constexpr (MODE == 3) {
+    if (ch == 0) {
+      int32_t* ob = off + (size_t)b * (K + 1);
+#pragma unroll
+      for (int i = 0; i < BPT; ++i)
+        if (t * BPT + i < K) ob[t * BPT + i] = bstart[i];
+      if (t == 0) ob[K] = n_valid;
+    }
+  }
   if (total_out && ch == 0 && t == 0) total_out[b] = n_valid;
   const int pmask = (int)((1u << pb) - 1u);
   if constexpr (MODE == 2) {
@@ -256,7 +282,7 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(
     // the last one the chunk past the end (always in the grid).  The chunk
     // of those low digits writes them, one thread per high digit.
     if (t < R) {
-      const int a = min(max(bstart + hrun, 0), n_valid);
+      const int a = min(max(bstart[0] + hrun[0], 0), n_valid);
       int32_t* ob = off + (size_t)b * (K + 1);
       for (int l = sel[3]; l <= sel[4]; ++l) {
         const int key = (t << lo_bits) | l;
@@ -268,8 +294,8 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(
   // rank in entry order within each wave (see above)
   const uint32_t blo = lane >= 32 ? ~0u : (1u << lane) - 1u;  // lanes below this one
   const uint32_t bhi = lane <= 32 ? 0u : ~0u >> (64 - lane);
-  // per step: digit (bits 0-7), rank (8-13), the digit group's lowest lane
-  // (16-21), 1 << 24 for an entry (every digit value of 8-bit digits is a real
+  // per step: digit (bits 0-7 or 0-9), rank (from bit RSH), the digit group's
+  // lowest lane (16-21), 1 << 24 for an entry (every digit value of 8-bit digits is a real
   // digit); and the count before the step
   int meta[STEPS], old[STEPS];
 #pragma unroll
@@ -295,7 +321,7 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(
     }
     const int rank = __popc(mlo & blo) + __popc(mhi & bhi);
     const int lead = !valid ? lane : mlo ? __builtin_ctz(mlo) : 32 + __builtin_ctz(mhi);
-    int ms = dg | (rank << 8) | (lead << 16) | (valid ? 1 << 24 : 0);
+    int ms = dg | (rank << RSH) | (lead << 16) | (valid ? 1 << 24 : 0);
     // one register per step from here on: the fields are read back from it,
     // not kept apart (which took four per step)
     asm volatile("" : "+v"(ms));
@@ -309,24 +335,29 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(
   }
 #pragma unroll
   for (int s = 0; s < STEPS; ++s)
-    old[s] = __shfl(old[s], (meta[s] >> 16) & 63) + ((meta[s] >> 8) & 63);
+    old[s] = __shfl(old[s], (meta[s] >> 16) & 63) + ((meta[s] >> RSH) & 63);
   __syncthreads();
   // this chunk's count per bin -> exclusive scan over bins; wave starts per bin
-  int c4[4], tot = 0;
+  int c4[BPT][4], tot = 0;
 #pragma unroll
-  for (int ww = 0; ww < 4; ++ww) {
-    c4[ww] = t < R ? cnt[ww][t] : 0;
-    tot += c4[ww];
-  }
-  int nloc;
-  const int ls = block_scan256(tot, wsum[1], nloc);
-  if (t < R) {
-    gdelta[t] = bstart + hrun - ls;  // output position = gdelta[digit] + sorted position
-    int run = ls;
+  for (int i = 0; i < BPT; ++i)
 #pragma unroll
     for (int ww = 0; ww < 4; ++ww) {
-      cnt[ww][t] = run;
-      run += c4[ww];
+      c4[i][ww] = t * BPT + i < R ? cnt[ww][t * BPT + i] : 0;
+      tot += c4[i][ww];
+    }
+  int nloc;
+  int run = block_scan256(tot, wsum[1], nloc);
+#pragma unroll
+  for (int i = 0; i < BPT; ++i) {
+    const int r = t * BPT + i;
+    if (r < R) {
+      gdelta[r] = bstart[i] + hrun[i] - run;  // output position = gdelta[digit] + sorted position
+#pragma unroll
+      for (int ww = 0; ww < 4; ++ww) {
+        cnt[ww][r] = run;
+        run += c4[i][ww];
+      }
     }
   }
   __syncthreads();
@@ -334,7 +365,7 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(
 #pragma unroll
   for (int s = 0; s < STEPS; ++s) {
     const int ms = meta[s];
-    const int dg = ms & 255;
+    const int dg = ms & ((1 << RSH) - 1);
     if (ms & (1 << 24)) {
       const int pos = cnt[w][dg] + old[s];
       int out;
@@ -343,11 +374,13 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(
         skey[pos] = k[s];
       } else if constexpr (MODE == 1) {  // high digit above the point id
         out = ((k[s] >> lo_bits) << pb) | (ibase + s * 64 + lane);
+      } else if constexpr (MODE == 3) {
+        out = ibase + s * 64 + lane;
       } else {  // the point id
         out = k[s] & pmask;
       }
       sval[pos] = out;
-      sdg[pos] = (uint8_t)dg;
+      sdg[pos] = (Digit)dg;
     }
   }
   __syncthreads();
@@ -932,19 +965,45 @@ static hipError_t launch_scatter(int dbits, dim3 grid, hipStream_t s, A... a) {
     case 6: radix_scatter_kernel<6, MODE><<<grid, 256, 0, s>>>(a...); break;
     case 7: radix_scatter_kernel<7, MODE><<<grid, 256, 0, s>>>(a...); break;
     case 8: radix_scatter_kernel<8, MODE><<<grid, 256, 0, s>>>(a...); break;
+    case 9:
+      if constexpr (MODE == 3) radix_scatter_kernel<9, MODE><<<grid, 256, 0, s>>>(a...);
+      else return hipErrorInvalidValue;
+      break;
+    case 10:
+      if constexpr (MODE == 3) radix_scatter_kernel<10, MODE><<<grid, 256, 0, s>>>(a...);
+      else return hipErrorInvalidValue;
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// Digit widths: the key needs `bits` bits; one pass for <= 8 bits, else two
-// passes of about half each.
-static void radix_plan(int64_t K, int& passes, int& d1, int& d2) {
+// Bits of a cluster id (at least 1).
+static int key_bits(int64_t K) {
   int bits = 1;
   while ((1ll << bits) < K) ++bits;
-  passes = bits <= RADIX_MAX_BITS ? 1 : 2;
-  d1 = passes == 1 ? bits : (bits + 1) / 2;
-  d2 = bits - (passes == 1 ? 0 : d1);
+  return bits;
+}
+
+// Digits of two plain passes: about half of the key each.
+static void radix_plan(int64_t K, int& d1, int& d2) {
+  d1 = (key_bits(K) + 1) / 2;
+  d2 = key_bits(K) - d1;
+}
+
+// One pass with a digit of the whole key: half the launches and traffic of two
+// passes, but runs of RADIX_CHUNK / K entries, whose writes the memory system
+// feels once they outgrow the caches, and a scan of B x R workgroups.  Measured,
+// two passes -> one (points x D, K; whole update): 20,000 x 128, 1,024: 52 ->
+// 38 us; 1M x 128, 1,024: 80 -> 69 (98 -> 86 with cold inputs); 4M x 128,
+// 1,024: 260 -> 255; 8M x 64, 1,024: 283 -> 298; 8M x 64, 512: 282 -> 266; 32 x
+// 65,536 x 128, 1,024 (32,768 scan workgroups): 190 -> 196.  Up to 256
+// clusters one pass it was, but with the sorted keys written and searched for
+// the offsets: 4M x 128, 256: 256 -> 231.
+static bool sort_one_pass(int64_t B, int64_t N, int64_t K) {
+  const int d = key_bits(K);
+  if (d <= RADIX_MAX_BITS) return true;
+  return K <= RADIX_ONE_R && (B << d) <= 8192 && B * N <= (d == 9 ? 1ll << 23 : 1ll << 22);
 }
 
 // Bits that hold a point id below N (at least 1).
@@ -959,8 +1018,7 @@ static int pid_bits(int64_t N) {
 // least a chunk on average) but at least what leaves the high digit <= 8
 // bits; within that, the split nearest to half.
 static void radix_plan_packed(int64_t N, int64_t K, int& d1, int& d2) {
-  int bits = 1;
-  while ((1ll << bits) < K) ++bits;
+  const int bits = key_bits(K);
   int fill = 0;
   while ((RADIX_CHUNK << (fill + 1)) <= N) ++fill;
   d1 = std::max(bits - RADIX_MAX_BITS, std::min((bits + 1) / 2, fill));
@@ -970,9 +1028,7 @@ static void radix_plan_packed(int64_t N, int64_t K, int& d1, int& d2) {
 // Two passes go over one array of packed words when the high digit and the
 // point id fit a non-negative int (31 bits).
 static bool sort_packed(int64_t N, int64_t K) {
-  int passes, d1, d2;
-  radix_plan(K, passes, d1, d2);
-  if (passes != 2) return false;
+  int d1, d2;
   radix_plan_packed(N, K, d1, d2);
   return d2 + pid_bits(N) <= 31;
 }
@@ -1001,9 +1057,26 @@ hipError_t launch_update(const void* X, int dt, const int32_t* idx, const float*
   hipError_t e;
   const int nch = (int)w.n_sort_chunks;
   const dim3 cgrid(nch, (unsigned)B);
-  int passes, d1, d2;
-  radix_plan(K, passes, d1, d2);
-  if (sort_packed(N, K)) {
+  int d1, d2;
+  if (sort_one_pass(B, N, K)) {
+    // the clusters are the bins; histograms and bin totals over the arrays of
+    // the two-pass sort (rhist .. keys_b: 4 R (chunks + 1) bytes an instance
+    // against 1,024 (chunks + 256) + 12 N)
+    const int d = key_bits(K), R = 1 << d;
+    int32_t* H = w.rhist;
+    int32_t* T = H + B * R * nch;
+    if (T + B * R > w.off) return hipErrorInvalidValue;
+    radix_hist_kernel<<<cgrid, 256, 0, s>>>(idx, (int)N, (int)K, nullptr, 0, R, nch, H, 0, nullptr,
+                                            0);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    radix_scan_kernel<<<dim3(R, (unsigned)B), 256, 0, s>>>(H, R, nch, R, T);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_scatter<3>(d, cgrid, s, idx, (const int32_t*)nullptr, (int)N, (int)K,
+                               (const int32_t*)nullptr, 0, nch, (const int32_t*)H,
+                               (const int32_t*)T, (int32_t*)nullptr, (int32_t*)nullptr, w.perm, 0,
+                               0, (const int32_t*)nullptr, w.off)) != hipSuccess)
+      return e;
+  } else if (sort_packed(N, K)) {
     radix_plan_packed(N, K, d1, d2);
     // two passes over one array: pass 1 sorts by the low digit and writes
     // (high digit, point id) words; pass 2 sorts those by the high digit in
@@ -1015,7 +1088,7 @@ hipError_t launch_update(const void* X, int dt, const int32_t* idx, const float*
     radix_hist_kernel<<<cgrid, 256, 0, s>>>(idx, (int)N, (int)K, nullptr, 0, R1, nch, w.rhist, 0,
                                             nullptr, 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    radix_scan_kernel<<<dim3(R1, (unsigned)B), 256, 0, s>>>(w.rhist, R1, nch, w.rbin1);
+    radix_scan_kernel<<<dim3(R1, (unsigned)B), 256, 0, s>>>(w.rhist, R1, nch, RADIX_MAX_R, w.rbin1);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_scatter<1>(d1, cgrid, s, idx, (const int32_t*)nullptr, (int)N, (int)K,
                                (const int32_t*)nullptr, 0, nch, (const int32_t*)w.rhist,
@@ -1026,7 +1099,7 @@ hipError_t launch_update(const void* X, int dt, const int32_t* idx, const float*
     radix_hist_kernel<<<cgrid2, 256, 0, s>>>(w.keys_a, (int)N, (int)K, nullptr, 0, R2, nch2,
                                              w.rhist, pb, w.rbin1, d1);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    radix_scan_kernel<<<dim3(R2, (unsigned)B), 256, 0, s>>>(w.rhist, R2, nch2, w.rbin);
+    radix_scan_kernel<<<dim3(R2, (unsigned)B), 256, 0, s>>>(w.rhist, R2, nch2, RADIX_MAX_R, w.rbin);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_scatter<2>(d2, cgrid2, s, (const int32_t*)w.keys_a, (const int32_t*)nullptr,
                                (int)N, (int)K, (const int32_t*)nullptr, d1, nch2,
@@ -1035,34 +1108,31 @@ hipError_t launch_update(const void* X, int dt, const int32_t* idx, const float*
                                (const int32_t*)w.rbin1, w.off)) != hipSuccess)
       return e;
   } else {
-    // pass 1: idx (raw) -> (keys_a, vals_a) sorted by the low digit; with one
-    // pass the values go straight to perm and the keys to keys_b
-    const int R = 1 << d1;
+    // more point ids than a packed word holds: pass 1 sorts idx by the low
+    // digit into (keys_a, vals_a), pass 2 those by the high digit
+    radix_plan(K, d1, d2);
+    const int R = 1 << d1, R2 = 1 << d2;
     radix_hist_kernel<<<cgrid, 256, 0, s>>>(idx, (int)N, (int)K, nullptr, 0, R, nch, w.rhist, 0,
                                             nullptr, 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    radix_scan_kernel<<<dim3(R, (unsigned)B), 256, 0, s>>>(w.rhist, R, nch, w.rbin);
+    radix_scan_kernel<<<dim3(R, (unsigned)B), 256, 0, s>>>(w.rhist, R, nch, RADIX_MAX_R, w.rbin);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_scatter<0>(d1, cgrid, s, idx, (const int32_t*)nullptr, (int)N, (int)K,
                                (const int32_t*)nullptr, 0, nch, (const int32_t*)w.rhist,
-                               (const int32_t*)w.rbin, w.rtotal,
-                               passes == 1 ? w.keys_b : w.keys_a, passes == 1 ? w.perm : w.vals_a,
-                               0, 0, (const int32_t*)nullptr, (int32_t*)nullptr)) != hipSuccess)
+                               (const int32_t*)w.rbin, w.rtotal, w.keys_a, w.vals_a, 0, 0,
+                               (const int32_t*)nullptr, (int32_t*)nullptr)) != hipSuccess)
       return e;
-    if (passes == 2) {
-      const int R2 = 1 << d2;
-      radix_hist_kernel<<<cgrid, 256, 0, s>>>(w.keys_a, (int)N, (int)K, w.rtotal, d1, R2, nch,
-                                              w.rhist, 0, nullptr, 0);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      radix_scan_kernel<<<dim3(R2, (unsigned)B), 256, 0, s>>>(w.rhist, R2, nch, w.rbin);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      if ((e = launch_scatter<0>(d2, cgrid, s, (const int32_t*)w.keys_a, (const int32_t*)w.vals_a,
-                                 (int)N, (int)K, (const int32_t*)w.rtotal, d1, nch,
-                                 (const int32_t*)w.rhist, (const int32_t*)w.rbin, (int32_t*)nullptr,
-                                 w.keys_b, w.perm, 0, 0, (const int32_t*)nullptr,
-                                 (int32_t*)nullptr)) != hipSuccess)  // the same total
-        return e;
-    }
+    radix_hist_kernel<<<cgrid, 256, 0, s>>>(w.keys_a, (int)N, (int)K, w.rtotal, d1, R2, nch,
+                                            w.rhist, 0, nullptr, 0);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    radix_scan_kernel<<<dim3(R2, (unsigned)B), 256, 0, s>>>(w.rhist, R2, nch, RADIX_MAX_R, w.rbin);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_scatter<0>(d2, cgrid, s, (const int32_t*)w.keys_a, (const int32_t*)w.vals_a,
+                               (int)N, (int)K, (const int32_t*)w.rtotal, d1, nch,
+                               (const int32_t*)w.rhist, (const int32_t*)w.rbin, (int32_t*)nullptr,
+                               w.keys_b, w.perm, 0, 0, (const int32_t*)nullptr,
+                               (int32_t*)nullptr)) != hipSuccess)  // the same total
+      return e;
     bounds_kernel<<<dim3((unsigned)((K + 1 + 255) / 256), (unsigned)B), 256, 0, s>>>(
         w.keys_b, w.rtotal, (int)N, (int)K, w.off);
     if ((e = hipGetLastError()) != hipSuccess) return e;
