@@ -47,16 +47,26 @@
 // so every stage issues the same loads and runs the same code: its MFMAs add
 // a finite x times zero, which is exactly zero.
 //
+// Calls with fewer than TILED_PLAIN point blocks, which super-tiles would put
+// on some of the XCDs only, go plainly in point-block order, and calls that
+// would leave CUs idle take fewer centroid blocks per workgroup (tiled_group;
+// the same bits).  2,000 x 512, K = 2,000: 106 -> 30 us; 10,000 x 512: 109 ->
+// 46; 16,000 x 1,024, K = 4,096: 208 -> 137; 40,000 x 512, K = 2,000 (157
+// blocks, as before): 125; 100,000 x 512, K = 4,096: 460 -> 433.
+//
 // Block order is XCD-aware: workgroup ids go round-robin over the 8 XCDs, and
 // each XCD walks super-tiles of 8 point blocks x all centroid groups (point
 // block fastest), so the workgroups resident on an XCD share both operands
 // through that XCD's L2.
+#include <algorithm>
+
 #include "fkm_device.h"
 
 namespace fkm {
 
 namespace {
 
+constexpr int TILED_PLAIN = 64;  // fewer point blocks: no super-tiles (launcher)
 constexpr int TT = 512;                  // threads per workgroup (8 waves)
 constexpr int BP = TILED_BP;             // points per workgroup
 constexpr int BC = TILED_BC;             // centroids per block
@@ -280,7 +290,7 @@ template <int DT>
 __global__ __launch_bounds__(TT, 1) void assign_tiled_kernel(
     const uint4* __restrict__ X, const uint4* __restrict__ chat, const float* __restrict__ cinit,
     const float* __restrict__ xnorm, const uint4* __restrict__ zero, int N, int D, int Kp, int npb,
-    int ncbg, uint64_t* __restrict__ keys) {
+    int ncbg, int cbpg, int plain, uint64_t* __restrict__ keys) {
   __shared__ __attribute__((aligned(16))) char buf0[STAGE];
   __shared__ __attribute__((aligned(16))) char buf1[STAGE];
   __shared__ __attribute__((aligned(16))) char buf2[STAGE];
@@ -292,15 +302,15 @@ __global__ __launch_bounds__(TT, 1) void assign_tiled_kernel(
   const int n = lane & 31, h = lane >> 5;
   const int wp = wave & 1, wc = wave >> 1;  // point half, centroid quarter
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int sup = j / (8 * ncbg), cbg = (j / 8) % ncbg;
-  const int pb = (sup * 8 + xcd) * 8 + (j & 7);
+  const int sup = j / (8 * ncbg), cbg = plain ? blockIdx.x / npb : (j / 8) % ncbg;
+  const int pb = plain ? blockIdx.x % npb : (sup * 8 + xcd) * 8 + (j & 7);
   if (pb >= npb) return;
   const int p0 = pb * BP;
   const int RC = D / 8;  // 16-byte chunks per row
   const int nds = D / DC;
   const int ndsv = (nds + 3) / 4 * 4;
-  const int cb0 = cbg * TILED_CBG;
-  const int ncbw = min(TILED_CBG, Kp / BC - cb0);  // centroid blocks of this workgroup
+  const int cb0 = cbg * cbpg;
+  const int ncbw = min(cbpg, Kp / BC - cb0);  // centroid blocks of this workgroup
 
   TiledCtx c;
   c.X = reinterpret_cast<const char*>(X + ((size_t)b * N + p0) * RC);
@@ -461,6 +471,20 @@ __global__ __launch_bounds__(256) void decode_keys_kernel(const uint64_t* __rest
   if (t == 0) objpart[(size_t)b * gridDim.x + blockIdx.x] = s[0];
 }
 
+// Centroid blocks per workgroup: TILED_CBG, or fewer where that leaves CUs idle:
+// the largest number with the least rounds of 256 workgroups x (blocks + 1),
+// one block standing for what a workgroup costs besides.
+static int tiled_group(int64_t point_blocks, int ncb) {
+  auto cost = [&](int64_t g) {
+    return (point_blocks * ((ncb + g - 1) / g) + 255) / 256 * (std::min<int64_t>(g, ncb) + 1);
+  };
+  int best = std::min(TILED_CBG, ncb);
+  if (point_blocks * ((ncb + best - 1) / best) >= 1024) return best;
+  for (int g = best - 1; g >= 1; --g)
+    if (cost(g) < cost(best)) best = g;
+  return best;
+}
+
 hipError_t launch_assign_tiled(const void* X, int dt, const Workspace& w, int64_t B, int64_t N,
                                int64_t D, int32_t* idx, float* min_dist, hipStream_t s) {
   if (D % DC != 0 || w.Kp % BC != 0) return hipErrorInvalidValue;
@@ -481,17 +505,19 @@ hipError_t launch_assign_tiled(const void* X, int dt, const Workspace& w, int64_
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int npb = (int)((N + BP - 1) / BP);
   const int ncb = (int)(w.Kp / BC);
-  const int ncbg = (ncb + TILED_CBG - 1) / TILED_CBG;
-  const int npb64 = (npb + 63) / 64 * 64;  // whole super-tiles on every XCD
+  const int cbpg = tiled_group(B * npb, ncb);
+  const int ncbg = (ncb + cbpg - 1) / cbpg;
+  const bool plain = npb < TILED_PLAIN;
+  const int npb64 = plain ? npb : (npb + 63) / 64 * 64;  // whole super-tiles on every XCD
   const dim3 grid((unsigned)(npb64 * ncbg), (unsigned)B);
   if (dt == DT_BF16)
     assign_tiled_kernel<DT_BF16><<<grid, TT, 0, s>>>((const uint4*)X, (const uint4*)w.chat,
                                                       w.cinit, w.xnorm, (const uint4*)(w.keys + nz),
-                                                      (int)N, (int)D, (int)w.Kp, npb, ncbg, w.keys);
+                                                      (int)N, (int)D, (int)w.Kp, npb, ncbg, cbpg, plain, w.keys);
   else
     assign_tiled_kernel<DT_F16><<<grid, TT, 0, s>>>((const uint4*)X, (const uint4*)w.chat,
                                                      w.cinit, w.xnorm, (const uint4*)(w.keys + nz),
-                                                     (int)N, (int)D, (int)w.Kp, npb, ncbg, w.keys);
+                                                     (int)N, (int)D, (int)w.Kp, npb, ncbg, cbpg, plain, w.keys);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   decode_keys_kernel<<<dim3((unsigned)w.n_assign_blocks, (unsigned)B), 256, 0, s>>>(
       w.keys, w.xnorm, (int)N, idx, min_dist, w.objpart);
