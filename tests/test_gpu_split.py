@@ -18,12 +18,14 @@ def km():
 
 
 # one point; a block and one more; 64-row stages (D = 256) with a short last
-# share; four point tiles a wave (D <= 64); widths that are padded; tie-heavy
+# share; four point tiles a wave (D <= 64); widths that are padded; rows past
+# 256 elements, whose workgroups take fewer centroid blocks; tie-heavy
 # duplicates are in every case (the second half of C
 # repeats the first)
 @pytest.mark.parametrize("N,D,K,dt,B", [
     (1, 128, 2050, "bf16", 513), (257, 128, 4100, "f16", 260), (130, 256, 3001, "bf16", 260),
     (513, 32, 5000, "f16", 260), (100, 100, 2500, "bf16", 520), (65, 200, 2222, "f16", 520),
+    (100, 320, 2500, "bf16", 260), (300, 512, 1100, "f16", 300),
 ])
 def test_shared_centroids_same_bits(km, N, D, K, dt, B):
     g = torch.Generator().manual_seed(N + D + K)
