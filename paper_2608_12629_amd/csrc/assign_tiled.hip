@@ -47,12 +47,15 @@
 // so every stage issues the same loads and runs the same code: its MFMAs add
 // a finite x times zero, which is exactly zero.
 //
-// Calls with fewer than TILED_PLAIN point blocks, which super-tiles would put
-// on some of the XCDs only, go plainly in point-block order, and calls that
-// would leave CUs idle take fewer centroid blocks per workgroup (tiled_group;
-// the same bits).  2,000 x 512, K = 2,000: 106 -> 30 us; 10,000 x 512: 109 ->
-// 46; 16,000 x 1,024, K = 4,096: 208 -> 137; 40,000 x 512, K = 2,000 (157
-// blocks, as before): 125; 100,000 x 512, K = 4,096: 460 -> 433.
+// Super-tiles give every XCD whole groups of 8 point blocks, so calls whose
+// point blocks fall short of a multiple of 64 by more than an eighth load the
+// XCDs unevenly: they go plainly in point-block order (79 blocks: 20,000 x
+// 1,024, K = 16,384: 900 -> 613 us; 32 x 20,000 x 512, K = 2,000: 2,049 ->
+// 1,426; 391 blocks: 437 -> 408; 196 blocks: 428 -> 434; but 2,048 blocks, 512k
+// x 1,024, K = 16,384, whose operands the XCDs' L2 then no longer share: 14.5
+// -> 16.0 ms).  Calls that would leave CUs idle take fewer centroid blocks per
+// workgroup (tiled_group; the same bits).  Both together: 2,000 x 512, K =
+// 2,000: 106 -> 30 us; 10,000 x 512: 109 -> 46; 20,000 x 512: 116 -> 64.
 //
 // Block order is XCD-aware: workgroup ids go round-robin over the 8 XCDs, and
 // each XCD walks super-tiles of 8 point blocks x all centroid groups (point
@@ -66,7 +69,6 @@ namespace fkm {
 
 namespace {
 
-constexpr int TILED_PLAIN = 64;  // fewer point blocks: no super-tiles (launcher)
 constexpr int TT = 512;                  // threads per workgroup (8 waves)
 constexpr int BP = TILED_BP;             // points per workgroup
 constexpr int BC = TILED_BC;             // centroids per block
@@ -507,8 +509,9 @@ hipError_t launch_assign_tiled(const void* X, int dt, const Workspace& w, int64_
   const int ncb = (int)(w.Kp / BC);
   const int cbpg = tiled_group(B * npb, ncb);
   const int ncbg = (ncb + cbpg - 1) / cbpg;
-  const bool plain = npb < TILED_PLAIN;
-  const int npb64 = plain ? npb : (npb + 63) / 64 * 64;  // whole super-tiles on every XCD
+  int npb64 = (npb + 63) / 64 * 64;  // whole super-tiles on every XCD
+  const bool plain = 8 * (int64_t)npb64 > 9 * (int64_t)npb;
+  if (plain) npb64 = npb;
   const dim3 grid((unsigned)(npb64 * ncbg), (unsigned)B);
   if (dt == DT_BF16)
     assign_tiled_kernel<DT_BF16><<<grid, TT, 0, s>>>((const uint4*)X, (const uint4*)w.chat,
