@@ -23,8 +23,6 @@ namespace fkm {
 
 namespace {
 
-constexpr int X3_MIN_SHARED = 16;
-
 template <int CP>
 struct X3Layout {
   static constexpr int D = 16 * CP, RC = 6 * CP, RCP = RC + 1;
@@ -173,56 +171,11 @@ __device__ __forceinline__ void x3_stage(int st, int nst, const char* img, int w
   __syncthreads();
 }
 
-// Score bits that order like the scores downwards (any sign), and back.
-__device__ __forceinline__ uint32_t x3_descending(float v) {
-  const uint32_t u = __float_as_uint(v);
-  return u & 0x80000000u ? u : ~u & 0x7fffffffu;
-}
-__device__ __forceinline__ float x3_score(uint32_t u) {
-  return __uint_as_float(u & 0x80000000u ? u : ~u & 0x7fffffffu);
-}
-
-// The points of a block from its shares' smallest key (the best score, of equal
-// ones the lowest centroid), with the bits and the objective partial that one
-// workgroup over all stages writes: each lane adds the same points.
-__global__ __launch_bounds__(256) void x3_merge_kernel(int N, int32_t* __restrict__ idx,
-                                                       float* __restrict__ min_dist,
-                                                       double* __restrict__ objpart, PipeSplit sp) {
-  __shared__ double lds_obj[4];
-  const int b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 31, h = lane >> 5;
-  double obj = 0.0;
-  {
-    const int pt = (blockIdx.x * 4 + wave) * 32 + n;
-    const bool ok = pt < N;
-    const uint64_t* kp = sp.keys + (size_t)b * sp.splits * N + (ok ? pt : 0);
-    uint64_t key = ~0ull;
-#pragma unroll 8
-    for (int s = h; s < sp.splits; s += 2) key = min(key, kp[(size_t)s * N]);
-    key = min(key, (uint64_t)__shfl_xor(key, 32));
-    if (h == 0 && ok) {
-      const float v = x3_score((uint32_t)(key >> 32)), xn = sp.xn[(size_t)b * N + pt];
-      const bool asg = xn <= __FLT_MAX__ && v > -__FLT_MAX__;
-      const float md = __builtin_fmaxf(__builtin_fmaf(-2.f, v, xn), 0.f);
-      idx[(size_t)b * N + pt] = asg ? (int)(uint32_t)key : -1;
-      min_dist[(size_t)b * N + pt] = asg ? md : __builtin_nanf("");
-      obj += asg ? (double)md : 0.0;
-    }
-  }
-#pragma unroll
-  for (int msk = 1; msk < 64; msk <<= 1) obj += __shfl_xor(obj, msk);
-  if (lane == 0) lds_obj[wave] = obj;
-  __syncthreads();
-  if (threadIdx.x == 0)
-    objpart[(size_t)b * gridDim.x + blockIdx.x] = ((lds_obj[0] + lds_obj[1]) + lds_obj[2]) + lds_obj[3];
-}
-
-// X [B,N,D] fp32; img [B, nst] stage images; blockIdx.z: the share of them.
+// X [B,N,D] fp32; img [B, nst] stage images.
 template <int CP, int NSUB>
 __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_x3_kernel(
     const float* __restrict__ X, const char* __restrict__ img, int N, int nst,
-    int32_t* __restrict__ idx, float* __restrict__ min_dist, double* __restrict__ objpart,
-    PipeSplit sp) {
+    int32_t* __restrict__ idx, float* __restrict__ min_dist, double* __restrict__ objpart) {
   using L = X3Layout<CP>;
   constexpr int D = L::D;
   __shared__ __attribute__((aligned(16))) char buf0[L::STAGE];
@@ -230,11 +183,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_x3_kernel(
   const int b = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, h = lane >> 5;
-  // the share's stages (calls with two point tiles a wave fill the chip: there
-  // the share's code is left out, which spilled 248 bytes at six chunks)
-  const int share = NSUB == 1 ? blockIdx.z : 0, st0 = NSUB == 1 ? share * sp.per : 0;
-  img += ((size_t)b * nst + st0) * L::STAGE;
-  if constexpr (NSUB == 1) nst = min(sp.per, nst - st0);
+  img += (size_t)b * nst * L::STAGE;
   x3_issue<CP>(img, 0, wave, lane, buf0);
 
   const int pbase = (blockIdx.x * 4 + wave) * 32 * NSUB;
@@ -308,21 +257,6 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_x3_kernel(
     }
   }
 
-  if (NSUB == 1 && sp.splits > 1) {
-#pragma unroll
-    for (int p = 0; p < NSUB; ++p) {
-      const int j = code[p] & 15;
-      const uint32_t i = st0 * L::TCS + (code[p] >> 4) * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-      const uint64_t key = (uint64_t)x3_descending(best[p]) << 32 | i;
-      const uint64_t ko = __shfl_xor(key, 32);
-      const int pt = pbase + p * 32 + n;
-      if (h == 0 && pt < N) {
-        sp.keys[((size_t)b * sp.splits + share) * N + pt] = key < ko ? key : ko;
-        if (share == 0) sp.xn[(size_t)b * N + pt] = xn[p];
-      }
-    }
-    return;
-  }
   double obj = 0.0;
 #pragma unroll
   for (int p = 0; p < NSUB; ++p) {
@@ -356,31 +290,13 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_x3_kernel(
 template <int CP>
 hipError_t launch_x3(const float* X, const Workspace& w, int64_t B, int64_t N, int64_t K,
                      int32_t* idx, float* min_dist, hipStream_t s) {
+  const dim3 grid((unsigned)w.n_assign_blocks, (unsigned)B), block(ASSIGN_THREADS);
   const int nst = (int)((K + X3Layout<CP>::TCS - 1) / X3Layout<CP>::TCS);
-  // Few points: shares of the stages as the 16-bit kernel takes them, their keys
-  // after the images.  Merging them is a launch of its own here (about 5 us),
-  // so only from X3_MIN_SHARED stages (about 1 us each) on: 5,000 x 64, K =
-  // 1,024: 18 us (49 with the fp32 instructions on 40 to 79 workgroups).
-  PipeSplit sp{1, nst, nullptr, nullptr, nullptr};
-  const size_t used = ((size_t)B * nst * X3Layout<CP>::STAGE + 255) & ~size_t(255);
-  const int nsub = x3_nsub(16 * CP, B * N);
-  if (nsub == 1 && nst >= X3_MIN_SHARED && used < w.ascr_bytes) {
-    Workspace rest = w;
-    rest.ascr += used;
-    rest.ascr_bytes -= used;
-    sp = pipe_split(rest, B, N, nst);
-  }
-  const dim3 grid((unsigned)w.n_assign_blocks, (unsigned)B, (unsigned)sp.splits);
-  const dim3 block(ASSIGN_THREADS);
-  if (nsub == 1) {
-    assign_x3_kernel<CP, 1><<<grid, block, 0, s>>>(X, w.img.p, (int)N, nst, idx, min_dist, w.objpart, sp);
+  if (x3_nsub(16 * CP, B * N) == 1) {
+    assign_x3_kernel<CP, 1><<<grid, block, 0, s>>>(X, w.img.p, (int)N, nst, idx, min_dist, w.objpart);
   } else if constexpr (CP <= X3_WIDE_CP) {
-    assign_x3_kernel<CP, 2><<<grid, block, 0, s>>>(X, w.img.p, (int)N, nst, idx, min_dist, w.objpart, sp);
+    assign_x3_kernel<CP, 2><<<grid, block, 0, s>>>(X, w.img.p, (int)N, nst, idx, min_dist, w.objpart);
   }
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || sp.splits == 1) return e;
-  const dim3 mgrid((unsigned)w.n_assign_blocks, (unsigned)B);
-  x3_merge_kernel<<<mgrid, 256, 0, s>>>((int)N, idx, min_dist, w.objpart, sp);
   return hipGetLastError();
 }
 
