@@ -15,7 +15,7 @@ LIB = os.path.join(HERE, "libflashkmeans.so")
 # the benchmark's in-run ceilings (include/fkm_calib.h), a library of its own
 CALIB_LIB = os.path.join(HERE, "libfkm_calib.so")
 CALIB_SOURCES = ["calib.hip"]
-SOURCES = ["api.hip", "assign.hip", "assign_f32.hip", "assign_pipe_bf16.hip", "assign_pipe_f16.hip",
+SOURCES = ["api.hip", "assign.hip", "assign_pipe_bf16.hip", "assign_pipe_f16.hip",
            "assign_smallk_bf16.hip", "assign_smallk_f16.hip", "assign_tiled.hip", "update.hip",
            "knn_bf16.hip", "knn_f16.hip", "knn_scan_bf16.hip", "knn_scan_f16.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -26,8 +26,7 @@ Workspace carve(void* base, int64_t B, int64_t N, int64_t D_user, int64_t K, int
   if (assign_tiled(dt, D)) {
     w.n_assign_blocks = (N + 255) / 256;  // the decode kernel's blocks
   } else {
-    w.x3 = x3_ok(dt, N, D, K);
-    const int64_t ppb = w.x3 ? 128 * x3_nsub(D, B * N) : assign_points_per_block(dt, D, B * N);
+    const int64_t ppb = assign_points_per_block(dt, D, B * N);
     w.n_assign_blocks = (N + ppb - 1) / ppb;
   }
   // fp32 workgroups shrink to 128 points for small problems: size the
@@ -59,7 +58,6 @@ Workspace carve(void* base, int64_t B, int64_t N, int64_t D_user, int64_t K, int
   w.keys_a = (int32_t*)take((size_t)(B * N) * 4);
   w.vals_a = (int32_t*)take((size_t)(B * N) * 4);
   w.keys_b = (int32_t*)take((size_t)(B * N) * 4);
-  const size_t off0 = o;
   w.off = (int32_t*)take((size_t)(B * (K + 1)) * 4);
   w.perm = (int32_t*)take((size_t)(B * N) * 4);
   w.carry = (float*)take((size_t)(red_slices_bound(B, N) * 2 * D) * 4);
@@ -71,16 +69,6 @@ Workspace carve(void* base, int64_t B, int64_t N, int64_t D_user, int64_t K, int
   w.pcount = (int32_t*)take(sk ? (size_t)(B * w.n_sk_chunks * K) * 4 : 0);
   w.ascr = (char*)w.rhist;
   w.ascr_bytes = o - upd0;
-  if (w.x3) {
-    w.img.p = w.ascr;
-    w.img.tcs = (int)X3_TCS(D);
-    w.img.Kst = (int)((K + X3_TCS(D) - 1) / X3_TCS(D) * X3_TCS(D));
-    w.img.D = (int)D;
-    w.img.stage = (int)x3_stage_bytes(D);
-    // below the offsets, carries, sums and partials that finalize and combine read
-    const size_t bytes = (size_t)(B * (w.img.Kst / w.img.tcs)) * (size_t)w.img.stage;
-    w.x3_tail = bytes <= off0 - upd0;
-  }
   const bool tiled = assign_tiled(dt, D);
   w.keys = (uint64_t*)take(tiled ? (size_t)(B * N + 1) * 8 + TILED_ZERO_BYTES : 0);
   w.xnorm = (float*)take(tiled ? (size_t)(B * N) * 4 : 0);
@@ -213,10 +201,6 @@ int kmeans_assign(const void* X, int xdtype, const float* C, int64_t B, int64_t 
     if ((rc = hip_status(pad_inputs(X, nullptr, xdtype, w, B, N, D, K, &a, s)))) return rc;
     Din = w.Dk;
   }
-  if (w.x3) {
-    if ((rc = hip_status(launch_prep3(C, w, B, K, D, s)))) return rc;
-    return hip_status(launch_assign_f32((const float*)a.X, w, B, N, w.Dk, K, idx, min_dist, s));
-  }
   if ((rc = hip_status(launch_prep(C, w.kdt, B, K, w.Kp, D, w.Dk, w.chat, w.cinit, s)))) return rc;
   return hip_status(launch_assign(a.X, w.kdt, w, B, N, Din, w.Dk, K, idx, min_dist, s));
 }
@@ -275,25 +259,12 @@ int kmeans_lloyd(const void* X, int xdtype, float* C, int64_t B, int64_t N, int6
   nx.nparts = sums_ok(kdt, Dk, K) ? w.n_sk_chunks : w.n_assign_blocks;
   nx.iters = iters;
   nx.objective = objective;
-  const X3Images img = w.x3 && w.x3_tail ? w.img : X3Images{};  // written by the update
-  nx.K = smallk_ok(kdt, Dk, K) ? 0 : (int)K;  // only the sort writes where the images lie
-  if (w.x3) {
-    nx.chat = nullptr;
-    if ((rc = hip_status(launch_prep3(a.C, w, B, K, Dk, s)))) return rc;
-  } else if ((rc = hip_status(launch_prep(a.C, kdt, B, K, w.Kp, Dk, Dk, w.chat, w.cinit, s))))
-    return rc;
+  if ((rc = hip_status(launch_prep(a.C, kdt, B, K, w.Kp, Dk, Dk, w.chat, w.cinit, s)))) return rc;
   for (int t = 0; t < iters; ++t) {
     nx.t = t;
-    nx.img = img;
-    if (t + 1 == iters) {  // no next iteration
-      nx.chat = nullptr;
-      nx.img.p = nullptr;
-    }
-    if (w.x3 && !img.p && t > 0 && (rc = hip_status(launch_prep3(a.C, w, B, K, Dk, s)))) return rc;
+    if (t + 1 == iters) nx.chat = nullptr;  // no next iteration
     if (fused)
       rc = hip_status(launch_sums(a.X, kdt, w, B, N, Dk, K, SUMS_FUSED, idx, min_dist, s));
-    else if (w.x3)
-      rc = hip_status(launch_assign_f32((const float*)a.X, w, B, N, Dk, K, idx, min_dist, s));
     else
       rc = hip_status(launch_assign(a.X, kdt, w, B, N, Dk, Dk, K, idx, min_dist, s));
     if (rc) return rc;

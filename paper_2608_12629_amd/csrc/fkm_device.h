@@ -106,39 +106,6 @@ __device__ inline void prep_row(const float* c, bool pad, int Dc, int D, int lan
   if (lane == 0) *cinit = zero ? -0x1.fffffep127f : -0.5f * ss;
 }
 
-// v = h + m + l in bf16 pieces, each the rounding of what the ones before leave.
-__device__ __forceinline__ void split3(float v, __bf16& h, __bf16& m, __bf16& l) {
-  h = (__bf16)v;
-  const float r = v - (float)h;  // exact
-  m = (__bf16)r;
-  l = (__bf16)(r - (float)m);
-}
-
-// prep_row for the fp32 assignment in three pieces: centroid k of instance b
-// into its stage image, and its score (prep_row's bits; the same padding rows).
-__device__ inline void prep3_row(const float* c, bool pad, int Dc, const X3Images& im, int64_t b,
-                                 int k, int lane) {
-  float v[4], ss = 0.f;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int d = lane + 64 * u;
-    v[u] = !pad && d < Dc ? c[d] : 0.f;
-    ss = __builtin_fmaf(v[u], v[u], ss);
-  }
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) ss += __shfl_xor(ss, m);
-  const bool zero = pad || !(ss <= __FLT_MAX__);
-  const int st = k / im.tcs, rr = k - st * im.tcs, row = (6 * (im.D / 16) + 1) * 16;
-  char* stage = im.p + (b * (im.Kst / im.tcs) + st) * im.stage;
-  __bf16* o = (__bf16*)(stage + rr * row);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int d = lane + 64 * u;
-    if (d < im.D) split3(zero ? 0.f : v[u], o[d], o[im.D + d], o[2 * im.D + d]);
-  }
-  if (lane == 0) ((float*)(stage + im.tcs * row))[rr] = zero ? -0x1.fffffep127f : -0.5f * ss;
-}
-
 // acc += A-chunk x B-chunk over the k-slice these two 16-byte chunks carry.
 template <int DT>
 __device__ inline f32x4 mfma_chunk(const uint4& a, const uint4& b, f32x4 acc) {

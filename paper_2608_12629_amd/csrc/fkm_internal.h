@@ -131,35 +131,6 @@ inline int64_t kernel_dim(int dt, int64_t D) {
 // over a handful is not small against 1e-3 |x|^2 when a point's nearest
 // centroids are far from it relative to its norm.
 inline int kernel_dt(int dt, int64_t D) { return dt != DT_F32 && D <= 16 ? DT_F32 : dt; }
-// fp32 points on the bf16 matrix cores in three pieces each (assign_f32.hip):
-// centroid stages of X3_TCS rows of 6 D bytes and a 16-byte gap, then their
-// scores, in whole KiB; two 32-point tiles a wave up to X3_WIDE_CP chunks of
-// 16 dimensions when that leaves two workgroups per CU, else one.
-constexpr int64_t X3_WIDE_CP = 6;
-constexpr int64_t X3_TCS(int64_t D) { return D <= 96 ? 64 : 32; }
-constexpr int64_t x3_stage_bytes(int64_t D) {
-  return (X3_TCS(D) * ((6 * (D / 16) + 1) * 16 + 4) + 1023) / 1024 * 1024;
-}
-inline int x3_nsub(int64_t D, int64_t BN) {
-  return D <= 16 * X3_WIDE_CP && BN >= (int64_t)512 * 256 ? 2 : 1;
-}
-// Against the fp32 matrix instructions (points x D, K): 65,536 x 64, 256: 26
-// -> 18 us; 500,000 x 32, 1,024: 301 -> 177; x 96: 788 -> 442; 200,000 x 192,
-// 1,024: 828 -> 390; x 256: 1,080 -> 599; and the error of min_dist (rms, of
-// its rms) 1.6e-7 -> 1.2e-7 at D = 32, 1.9e-7 -> 1.3e-7 at 96, 2.9e-7 ->
-// 1.4e-7 at 256.  Rows of 16 stay with the fp32 instructions, whose 16 products
-// leave less to gain (174 -> 110 us at 500,000, K = 1,024) and whose error is
-// the smaller one there (3 of 16 used: 1.8e-7 against 2.3e-7).
-// The stage images lie in the update's part of the workspace: they have to fit
-// into what the sort and the sums take there, per instance.  Where they do not
-// (2 K D > 16 N + 262,144 and a little, many wide clusters of few points each)
-// the fp32 instructions stay.
-inline bool x3_ok(int dt, int64_t N, int64_t D, int64_t K) {
-  const int64_t img = (K + X3_TCS(D) - 1) / X3_TCS(D) * x3_stage_bytes(D);
-  const int64_t nch = (N + RADIX_CHUNK - 1) / RADIX_CHUNK;
-  return dt == DT_F32 && D >= 32 && D <= 256 &&
-         img <= 4 * RADIX_MAX_R * (nch + RADIX_MAX_R) + 16 * N + 4 * K * D;
-}
 // Tiled kernel: 256 points x 256-centroid blocks, TILED_CBG blocks per
 // workgroup; its centroids are padded to whole blocks.
 constexpr int TILED_BP = 256, TILED_BC = 256, TILED_CBG = 8;
@@ -167,11 +138,6 @@ constexpr int64_t TILED_ZERO_BYTES = 16384;  // zeros after the keys (padding st
 inline int64_t kpad_for(int dt, int64_t D, int64_t K) {
   return assign_tiled(dt, D) ? (K + TILED_BC - 1) / TILED_BC * TILED_BC : kpad(K);
 }
-
-struct X3Images {
-  char* p;              // [B, Kst / tcs] stages
-  int Kst, tcs, D, stage;  // rows per instance, rows per stage, row width, bytes per stage
-};
 
 // ---- workspace layout -------------------------------------------------------
 struct Workspace {
@@ -198,9 +164,6 @@ struct Workspace {
   // its scratch, in which a split assignment keeps its shares' results.
   char* ascr;
   size_t ascr_bytes;
-  bool x3;         // fp32 points run in three bf16 pieces (x3_ok)
-  bool x3_tail;    // the images fit below what the update's last kernel reads
-  X3Images img;    // at ascr
   void* xpad;      // [B,N,Dk] the points in zero-padded rows of type kdt (only when copied)
   float* cpad;     // [B,K,Dk] the centroids in zero-padded rows (only when copied)
   int64_t Dk;      // the row width the kernels run at (kernel_dim)
@@ -220,8 +183,6 @@ struct NextStep {
   void* chat = nullptr;          // [B,Kp,D]; nullptr: not written
   float* cinit = nullptr;        // [B,Kp]
   int64_t Kp = 0;
-  X3Images img{};                // img.p: written in place of chat and cinit
-  int K = 0;                     // clusters whose waves write padding rows too; 0: none to write
   const double* objpart = nullptr;
   int64_t nparts = 0;            // objective partials per instance
   int iters = 0, t = 0;
@@ -236,12 +197,6 @@ hipError_t launch_prep(const float* C, int dt, int64_t B, int64_t K, int64_t Kp,
 hipError_t launch_assign(const void* X, int dt, const Workspace& w, int64_t B, int64_t N,
                          int64_t Din, int64_t D, int64_t K, int32_t* idx, float* min_dist,
                          hipStream_t s);
-// The fp32 assignment in three pieces (w.x3): the centroids C [B,K,Dc] into
-// the images, and the assignment from them.
-hipError_t launch_prep3(const float* C, const Workspace& w, int64_t B, int64_t K, int64_t Dc,
-                        hipStream_t s);
-hipError_t launch_assign_f32(const float* X, const Workspace& w, int64_t B, int64_t N, int64_t D,
-                             int64_t K, int32_t* idx, float* min_dist, hipStream_t s);
 hipError_t launch_pipe_bf16(const void* X, const Workspace& w, int64_t B, int64_t N, int64_t Din,
                            int64_t D, int32_t* idx, float* min_dist, hipStream_t s);
 hipError_t launch_pipe_f16(const void* X, const Workspace& w, int64_t B, int64_t N, int64_t Din,

@@ -562,13 +562,6 @@ __device__ inline void next_step_tail(const NextStep& nx, const float* row, int6
     else if (nx.dt == DT_F16) prep_row<DT_F16>(row, false, D, D, tt, out, nx.cinit + r);
     else prep_row<DT_F32>(row, false, D, D, tt, out, nx.cinit + r);
   }
-  if (nx.img.p && has_row && tt < 64) {
-    prep3_row(row, false, D, nx.img, b, k, tt);
-    // where a sort has overwritten the images' padding rows, cluster k writes
-    // every K-th of them (K > 64 there: at most one)
-    if (nx.K)
-      for (int i = nx.K + k; i < nx.img.Kst; i += nx.K) prep3_row(row, true, D, nx.img, b, i, tt);
-  }
   if (nx.objective && obj_block) {
     // a thread adds its partials (every 256th) in index order; the loads go
     // out OBJ_BATCH at a time (there can be tens of thousands of partials,

@@ -26,6 +26,7 @@ def km():
     (1, 128, 2050, "bf16", 513), (257, 128, 4100, "f16", 260), (130, 256, 3001, "bf16", 260),
     (513, 32, 5000, "f16", 260), (100, 100, 2500, "bf16", 520), (65, 200, 2222, "f16", 520),
     (100, 320, 2500, "bf16", 260), (300, 512, 1100, "f16", 300),
+    (100, 64, 1100, "f32", 520), (257, 96, 1030, "f32", 300), (200, 128, 600, "f32", 400),
 ])
 def test_shared_centroids_same_bits(km, N, D, K, dt, B):
     g = torch.Generator().manual_seed(N + D + K)
