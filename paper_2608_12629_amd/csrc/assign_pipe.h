@@ -49,7 +49,7 @@ namespace fkm {
 // sign, reads as an integer above every finite negative key and never wins.
 // Non-finite values: a centroid with a NaN or infinite coordinate scores NaN
 // or -inf against every point and never wins; a point whose squared norm is
-// not finite, or whose best score is not above -FLT_MAX (no real centroid
+// not finite, or whose best score is not above MASKED_PAD (no real centroid
 // scored finitely), is left unassigned (idx -1, min_dist NaN, no objective
 // term), and such points do not enter the workgroup's shift.
 typedef __attribute__((address_space(1))) void global_void;
@@ -499,7 +499,7 @@ __device__ __forceinline__ void pipe_block(int blk, const uint4* __restrict__ X,
     const int pt = pbase + p * 32 + n;
     if (h == 0 && pt < N) {
       // unassigned: a norm that is not finite, or no real centroid's score finite
-      const bool asg = xn[p] <= __FLT_MAX__ && v > -__FLT_MAX__;
+      const bool asg = xn[p] <= __FLT_MAX__ && v > MASKED_PAD;
       const float md = __builtin_fmaxf(__builtin_fmaf(-2.f, v + (PPQ ? Qp[p] : Q), xn[p]), 0.f);
       idx[pt] = asg ? i : -1;
       min_dist[pt] = asg ? md : __builtin_nanf("");
@@ -538,7 +538,7 @@ __device__ __forceinline__ void pipe_merge_block(int blk, int N, int32_t* __rest
     key = min(key, (uint64_t)__shfl_xor(key, 32));
     if (h == 0 && ok) {
       const float v = __uint_as_float((uint32_t)(key >> 32)), xn = sp.xn[pt];
-      const bool asg = xn <= __FLT_MAX__ && v > -__FLT_MAX__;
+      const bool asg = xn <= __FLT_MAX__ && v > MASKED_PAD;
       const float md = __builtin_fmaxf(__builtin_fmaf(-2.f, v + Q, xn), 0.f);
       idx[pt] = asg ? (int)(uint32_t)key : -1;
       min_dist[pt] = asg ? md : __builtin_nanf("");

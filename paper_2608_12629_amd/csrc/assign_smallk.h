@@ -250,7 +250,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 2) void assign_smallk_kernel(
       v = take ? vo : v;
       i = take ? io : i;
       // unassigned: a norm that is not finite, or no real centroid's score finite
-      const bool asg = ss <= __FLT_MAX__ && v > -__FLT_MAX__;
+      const bool asg = ss <= __FLT_MAX__ && v > MASKED_PAD;
       i = asg ? i : -1;
       if (h == 0) {
         const float md = __builtin_fmaxf(__builtin_fmaf(-2.f, v + Qp[0], ss), 0.f);

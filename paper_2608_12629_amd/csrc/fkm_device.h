@@ -69,6 +69,11 @@ __device__ inline float tree_sumsq(const uint4 (&a)[CPL]) {
   return tree_sumsq_of<DT, CPL>([&](int c) { return a[c]; });
 }
 
+// A padding row's score (-FLT_MAX, the shift lost in its rounding) once its low
+// four bits have held a row position and are cleared again: a best score read
+// back from such a key is a real centroid's only above this.
+constexpr float MASKED_PAD = -0x1.ffffe0p127f;
+
 // One centroid row for the assignment: c^ = round(c) to the storage type
 // into out (D elements) and -|c^|^2 / 2 into *cinit (a padding row: zeros and
 // -FLT_MAX), by one wave: the squares are summed lane-strided and then by a

@@ -154,3 +154,53 @@ def test_nonfinite(km, oracle, name):
     # bit patterns: the planted centroids stay NaN on both sides
     assert torch.equal(CT.view(torch.int32), Cg.view(torch.int32)), \
         "T single iterations differ from one T-iteration call"
+
+
+# one shape per kernel: B, N, D, K, dtype
+NO_CENTROID = {
+    "f32": (1, 700, 64, 100, torch.float32),
+    "streaming": (1, 700, 128, 300, torch.bfloat16),
+    "streaming_f16": (2, 700, 256, 40, torch.float16),
+    "shared": (1, 100, 128, 4100, torch.bfloat16),      # shares of the centroids, merged
+    "rows_in_place": (1, 700, 100, 300, torch.float16),
+    "wide_spread": (1, 700, 128, 300, torch.bfloat16),  # each point's own shift
+    "one_hot": (1, 3000, 64, 64, torch.float16),         # small-K sums / fused step
+    "tiled": (1, 700, 320, 300, torch.bfloat16),
+    "widened": (1, 700, 8, 40, torch.bfloat16),
+}
+
+
+@pytest.mark.parametrize("only", [None, 0, -1])
+@pytest.mark.parametrize("name", list(NO_CENTROID))
+@pytest.mark.parametrize("K1", [False, True])
+def test_no_finite_centroid(km, name, K1, only):
+    """Every centroid NaN or infinite: every point is unassigned, the objective is
+    0, no centroid changes.  With one finite centroid (the first or the last)
+    every point takes it."""
+    B, N, D, K, dt = NO_CENTROID[name]
+    if K1:
+        K = 1
+    g = torch.Generator().manual_seed(K + N)
+    X = torch.randn((B, N, D), generator=g)
+    if name == "wide_spread":
+        X[:, ::3] *= 100.0
+    C = torch.randn((B, K, D), generator=g)
+    C[..., 0] = float("nan")
+    C[:, 1::2, 0] = float("inf")
+    C[:, ::5, D - 1] = float("-inf")
+    if only is not None:
+        C[:, only] = 0.5
+    X, C = X.to(dt).cuda(), C.cuda()
+    idx, md = km.kmeans_assign(X, C)
+    Cl, idx_l, md_l, n, J = km.kmeans_lloyd(X, C.clone(), 2)
+    torch.cuda.synchronize()
+    if only is None:
+        for i, m in ((idx, md), (idx_l, md_l)):
+            assert bool((i == -1).all()) and bool(m.isnan().all())
+        assert bool((J == 0).all()) and bool((n == 0).all())
+        assert torch.equal(Cl.view(torch.int32), C.view(torch.int32))
+    else:
+        want = only % K
+        assert bool((idx == want).all()) and bool((idx_l == want).all())
+        assert bool(md.isfinite().all()) and bool(J.isfinite().all())
+        assert bool((n[:, want] == N).all())
