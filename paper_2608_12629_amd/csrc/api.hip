@@ -4,6 +4,7 @@
 // the arguments have been validated.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstring>
 #include <mutex>
 
@@ -306,7 +307,7 @@ static int knn_check_sizes(int64_t B, int64_t M, int64_t N, int64_t D, int64_t k
   return FKM_OK;
 }
 
-// How a search runs.  Few queries: the scan (knn_scan.h).  More: the list kernel
+// How a search runs.  Few queries: the scan (knn_scan.h).  Others: the list kernel
 // over `splits` shares of the rows, which fill the chip when the query blocks
 // do not.  Either needs scratch (the scan's group maxima, the shares' lists);
 // with less than that the list kernel runs unsplit, which needs none.
@@ -337,49 +338,82 @@ static KnnScanPlan knn_scan_plan(int64_t B, int64_t M, int64_t N, int64_t Dk) {
   return p;
 }
 
-// Shares per query block: the fewest rounds of resident workgroups times the
-// stages of a share plus what starting a share, filling its empty lists and
-// merging them cost, in stages (12, or 256 with 32-entry lists, whose
-// insertions take most of the time).  Measured, D = 128: 65,536 queries in
-// 1,048,576 rows 18,291 us unsplit, 15,690 in 2 shares, 17,854 in 3; 4,096 in
-// 100,000 3,276 unsplit, 342 in 32, 423 in 48; 20,000 in 1,000,000 with k = 32
-// 27,068 unsplit, 25,712 in 3, 32,047 in 8.
-static int knn_splits(int64_t B, int64_t M, int64_t N, int64_t Dk, int k) {
-  const int64_t nst = kpad(N) / (Dk <= 128 ? 128 : 64);
-  const int64_t qpb = k <= 16 && Dk <= 128 ? 256 : 128;  // queries per workgroup
-  const int64_t slots = k <= 16 ? 512 : 256;             // resident workgroups
-  const int64_t qb = (M + qpb - 1) / qpb * B, extra = k <= 16 ? 12 : 256;
-  int64_t best = 1, cost = INT64_MAX;
-  for (int64_t s = 1; s <= KNN_MAX_SPLITS && s <= nst; ++s) {
-    const int64_t c = (qb * s + slots - 1) / slots * ((nst + s - 1) / s + extra);
-    if (c < cost) cost = c, best = s;
-  }
-  return (int)best;
+// What the routes take, in us: fitted to times over B = 1 .. 100, M = 1 .. 8,192, N
+// = 64 .. 1,000,000, D = 16 .. 256, k = 1 .. 32, bf16 (1,961 shapes; the list
+// kernel within 17%, one standard deviation, the scan too).
+//
+// The list kernel over s shares of the rows: rounds of resident workgroups (a
+// chip more than half full of those with up to 16 entries runs 1.2 times slower),
+// each its stages and the filling of its lists, whose insertions thin out as
+// the lists improve (about the root of the stages); and for a split the merge,
+// a step per entry, whose throughput counts for many queries.
+static double knn_list_us(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, int64_t s) {
+  const bool wide = Dk > 128, large = k > 16;
+  const int64_t nst = kpad(N) / (wide ? 64 : 128), n = (nst + s - 1) / s;
+  const int64_t qpb = !large && !wide ? 256 : 128;  // queries per workgroup
+  const int64_t slots = large ? 256 : 512;           // resident workgroups
+  const int64_t wgs = (M + qpb - 1) / qpb * B * s;
+  const double rounds = (double)((wgs + slots - 1) / slots);
+  const double load = large ? rounds : 2 * wgs <= slots ? 1.0 : 1.2 * rounds;
+  const int entries = k <= 8 ? 8 : k <= 10 ? 10 : k <= 16 ? 16 : KNN_MAX_K;
+  const double stage = (wide ? 1.4 : 1.3 + 1.4 * (double)Dk / 128) * (large ? 1.25 : 1.0);
+  const double fill = (wide ? (large ? 2.1 : 1.67) : large ? 3.1 : 3.85) * entries;
+  double us = load * (1.3 + stage * (double)n + fill * (std::sqrt((double)n) - 0.05));
+  if (s > 1) us += 5 + k + (double)(B * M) * 1e-4 * (4 + k) * (wide ? 1.8 : 1.0);
+  return us;
 }
 
+// The scan: its stages over 512 resident workgroups, and one pick workgroup per
+// query, whose tile buffers leave one on a CU (three for rows of up to 32
+// elements); with fewer groups than k every row is ranked against every other.
+static double knn_scan_us(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, const KnnScanPlan& p) {
+  const bool wide = Dk > 128;
+  const int64_t nst = kpad(N) / (wide ? 64 : 128);
+  const double tiles = (double)(std::min<int64_t>(k, p.ngroups) << p.gs);
+  double pick = wide ? 0.025 + 0.00117 * tiles : 0.0213 + 0.00065 * tiles;
+  if (p.ngroups < k) pick += 5.4e-5 * (double)(N * ((N + 511) / 512));  // 512 threads
+  if (Dk <= 32) pick /= 3;
+  const double stage = 0.2 + 2.85 * (double)std::min<int64_t>(Dk, 128) / 128;
+  return 8.5 + std::max(7.0, (double)(B * M) * pick) +
+         (double)((M + 127) / 128 * B * nst) / 512 * stage;
+}
+
+// The route of a search.  The list kernel's shares: the number of the least
+// estimate, where that saves a tenth (65,536 queries in 1,048,576 x 128, k = 10:
+// 18,291 us unsplit, 15,690 in 2 shares, 17,854 in 3; 4,096 in 100,000: 3,276
+// unsplit, 342 in 32; but 16 x 4,096 in 300: 77 unsplit, 180 in 2).  The scan
+// where it is estimated faster than that (100 queries in 1,000,003 x 128, k = 10:
+// 71 us against 803 in shares, 2,048: 820 / 1,009), and up to 2,048 queries an
+// instance (1,024 past D = 128; four times that for more than 16 neighbours).
+// Its picks cost a workgroup per query, so many instances leave it early: 64 x
+// 2,048 in 64: 3,470 us, the list kernel 57; 64 x 512 in 1,000 x 128, k = 32:
+// 4,890 / 320; 16 x 1,024 in 300 x 256: 871 / 52.  A few queries, for which no
+// split can be as fast, are told by one estimate (the others take 2 us on the host).
 static KnnPlan knn_plan(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, size_t scratch) {
   KnnPlan p{};
   p.splits = 1;
-  // Where the scan gives way (times of both at N = 1,000,003, D = 128, k = 10: M
-  // = 128 71 against 803 us, 1,024 424 / 808, 2,048 820 / 1,009, 4,096 1,608 /
-  // 1,639; N = 10,000: M = 2,048 93 / 105, 4,096 172 / 126; N = 400,000, D =
-  // 256: M = 1,024 364 / 421, 2,048 671 / 672; with 32-entry lists, one wave per
-  // SIMD, M = 4,096 at N = 1,000,003: 2,123 / 6,475).
   const int64_t lim = k > 16 ? (Dk > 128 ? 4096 : 8192) : Dk > 128 ? 1024 : 2048;
+  double scan = HUGE_VAL;
   if (M <= lim) {
     p.sc = knn_scan_plan(B, M, N, Dk);
     p.scratch = (size_t)(B * M * p.sc.ngroups) * 4;
     // its maxima take no more than a copy of the rows would (or 64 MiB)
     const size_t most = std::max((size_t)(B * kpad(N) * Dk) * 2, (size_t)64 << 20);
-    p.scan = p.scratch <= std::min(scratch, most);
-    if (p.scan) return p;
+    if (p.scratch <= std::min(scratch, most)) scan = knn_scan_us(B, M, N, Dk, k, p.sc);
   }
-  p.splits = knn_splits(B, M, N, Dk, k);
-  p.scratch = p.splits > 1 ? (size_t)(B * M * p.splits * k) * 8 : 0;
-  if (p.scratch > scratch) {
-    p.splits = 1;
-    p.scratch = 0;
+  p.scan = scan <= knn_list_us(1, 1, 1, Dk, k, 1);  // less than the list kernel takes at the least
+  if (p.scan) return p;
+  const int64_t nst = kpad(N) / (Dk <= 128 ? 128 : 64);
+  const size_t one = (size_t)(B * M * k) * 8;  // a share's lists
+  const double whole = knn_list_us(B, M, N, Dk, k, 1);
+  double list = whole;
+  for (int64_t s = 2; s <= KNN_MAX_SPLITS && s <= nst && s * one <= scratch; ++s) {
+    const double us = knn_list_us(B, M, N, Dk, k, s);
+    if (us < list) list = us, p.splits = (int)s;
   }
+  if (list > 0.9 * whole) list = whole, p.splits = 1;
+  p.scan = scan <= list;
+  if (!p.scan) p.scratch = p.splits > 1 ? p.splits * one : 0;
   return p;
 }
 
@@ -424,6 +458,16 @@ size_t kmeans_knn_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t D, in
   const KnnWs w = knn_carve(nullptr, B, M, N, D);
   const size_t want = w.scratch_at + knn_plan(B, M, N, w.Dk, k, SIZE_MAX).scratch;
   return want > w.fixed ? want : w.fixed;
+}
+
+// For tests, not in the public header: the route of a search with a workspace of
+// ws_bytes; 0 the scan, else the list kernel's shares of the rows; -1 refused.
+int fkm_knn_route(int64_t B, int64_t M, int64_t N, int64_t D, int k, int xdtype, size_t ws_bytes) {
+  if (knn_check_sizes(B, M, N, D, k, xdtype) != FKM_OK) return -1;
+  const KnnWs w = knn_carve(nullptr, B, M, N, D);
+  if (ws_bytes < w.fixed) return -1;
+  const KnnPlan p = knn_plan(B, M, N, w.Dk, k, ws_bytes - w.scratch_at);
+  return p.scan ? 0 : p.splits;
 }
 
 int kmeans_knn(const void* Q, const void* R, int xdtype, int64_t B, int64_t M, int64_t N, int64_t D,

@@ -224,6 +224,52 @@ def test_knn_rejections(lib):
     assert kw(N=1000) >= kw(N=100)
 
 
+def _route(lib, B, M, N, D, k, dt=BF16, wsb=None):
+    lib.fkm_knn_route.argtypes = [ctypes.c_int64] * 4 + [ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
+    return lib.fkm_knn_route(B, M, N, D, k, dt, 1 << 50 if wsb is None else wsb)
+
+
+# us measured on an MI355X, bf16: the scan, the list kernel unsplit, in shares
+# (0: never taken at that size)
+@pytest.mark.parametrize("B,M,N,D,k,scan,whole,shares", [
+    (1, 1, 64, 128, 10, 15, 38, 0), (1, 100, 1_000_003, 128, 10, 71, 15_730, 803),
+    (1, 256, 300, 128, 10, 18, 74, 60), (1, 1024, 100_000, 128, 10, 98, 3175, 179),
+    (1, 2048, 1_000_000, 128, 10, 776, 17_800, 994), (1, 4096, 300, 128, 32, 188, 193, 148),
+    (4, 8, 1000, 32, 10, 17, 81, 48), (1, 512, 1_000_000, 32, 10, 93, 12_183, 664),
+    (64, 2048, 64, 128, 1, 3106, 47, 0), (64, 2048, 64, 128, 10, 3470, 56, 0),
+    (64, 2048, 300, 128, 10, 5858, 106, 103), (64, 1024, 64, 256, 10, 2050, 43, 0),
+    (64, 1024, 300, 256, 10, 3445, 77, 0), (16, 2048, 64, 128, 10, 860, 41, 0),
+    (64, 512, 1000, 128, 32, 4890, 330, 320), (16, 8192, 1000, 128, 32, 19_492, 1201, 1229),
+    (16, 1024, 300, 256, 10, 871, 52, 92), (64, 2048, 3000, 32, 10, 1482, 298, 271),
+    (1, 65_536, 1_048_576, 128, 10, 0, 18_291, 15_690), (1, 4096, 100_000, 32, 32, 152, 7512, 1142),
+    (16, 4096, 300, 128, 10, 0, 77, 180), (16, 4096, 1000, 128, 10, 0, 134, 225),
+    (64, 1024, 1000, 32, 10, 747, 129, 195), (4, 4096, 64, 256, 10, 506, 27, 79),
+    (1, 256, 64, 256, 32, 16, 88, 109), (16, 1024, 300, 128, 32, 731, 186, 249),
+])
+def test_knn_route_is_the_fastest_measured(lib, B, M, N, D, k, scan, whole, shares):
+    """The route takes at most a quarter more than the fastest of the three."""
+    r = _route(lib, B, M, N, D, k)
+    took = scan if r == 0 else whole if r == 1 else shares
+    best = min(t for t in (scan, whole, shares) if t)
+    assert took and took <= 1.25 * best, (r, took, best)
+
+
+def test_knn_route_and_workspace(lib):
+    """A search runs in any workspace that holds a copy of the rows: with less than the scan's
+    maxima or the shares' lists need, by a route that fits."""
+    full = lambda *a: lib.kmeans_knn_workspace_bytes(*a, BF16)
+    for B, M, N, D, k in [(1, 100, 1_000_003, 128, 10), (1, 2048, 3000, 16, 32), (1, 40, 9_000, 40, 12),
+                          (2, 2_100, 700, 24, 16), (1, 65_536, 1_048_576, 128, 10), (1, 30, 70, 16, 5)]:
+        up = lambda v: (v + 255) // 256 * 256
+        Np, Dk = (N + 127) // 128 * 128, (D + 15) // 16 * 16
+        least = up(B * Np * Dk * 2) + up(B * Np * 4) + (up(B * M * Dk * 2) if Dk != D else 0)
+        assert full(B, M, N, D, k) >= least
+        assert _route(lib, B, M, N, D, k, wsb=least - 1) == -1
+        assert _route(lib, B, M, N, D, k, wsb=least) >= 0
+        assert _route(lib, B, M, N, D, k, wsb=full(B, M, N, D, k)) == _route(lib, B, M, N, D, k)
+    assert _route(lib, 1, 10, 20, 64, 21) == -1 and _route(lib, 1, 10, 20, 64, 4, F32) == -1
+
+
 def test_calibration_library_exports_its_header():
     """libfkm_calib.so (the benchmark's in-run ceilings) exports every call that
     include/fkm_calib.h declares and rejects bad arguments on the host."""
