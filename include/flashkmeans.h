@@ -174,10 +174,12 @@ int kmeans_lloyd_noalloc(const void* X, int xdtype, float* C, int64_t B, int64_t
  * so rows whose distances differ by less than that rounding may trade places.
  * The workspace holds the scores of R's rows, zero-padded copies of R and Q
  * where D is not a multiple of 16, and lists or group maxima that let few
- * queries fill the GPU: kmeans_knn_workspace_bytes bytes.  A call accepts any
- * workspace that holds the first two and at least a copy of R (the size that
- * was asked for before there was the third); with less than the full size it
- * may run slower, with the same results.
+ * queries fill the GPU (at most a copy of R, or 64 MiB):
+ * kmeans_knn_workspace_bytes bytes, which for fixed B, D, k and dtype never
+ * decrease as M or N grows, so a workspace sized for the largest calls serves
+ * all.  A call accepts any workspace that holds the first two and at least a
+ * copy of R (the size that was asked for before there was the third); with less
+ * than the full size it may run slower, with the same results.
  */
 size_t kmeans_knn_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t D, int k, int xdtype);
 int kmeans_knn(const void* Q, const void* R, int xdtype, int64_t B, int64_t M, int64_t N, int64_t D,

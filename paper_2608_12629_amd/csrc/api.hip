@@ -389,17 +389,23 @@ static double knn_scan_us(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, co
 // 2,048 in 64: 3,470 us, the list kernel 57; 64 x 512 in 1,000 x 128, k = 32:
 // 4,890 / 320; 16 x 1,024 in 300 x 256: 871 / 52.  A few queries, for which no
 // split can be as fast, are told by one estimate (the others take 2 us on the host).
+static int64_t knn_scan_limit(int64_t Dk, int k) {
+  return k > 16 ? (Dk > 128 ? 4096 : 8192) : Dk > 128 ? 1024 : 2048;
+}
+// The scan's maxima or the shares' lists take no more than a copy of the rows
+// would (or 64 MiB).
+static size_t knn_most_scratch(int64_t B, int64_t N, int64_t Dk) {
+  return std::max((size_t)(B * kpad(N) * Dk) * 2, (size_t)64 << 20);
+}
 static KnnPlan knn_plan(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, size_t scratch) {
   KnnPlan p{};
   p.splits = 1;
-  const int64_t lim = k > 16 ? (Dk > 128 ? 4096 : 8192) : Dk > 128 ? 1024 : 2048;
+  scratch = std::min(scratch, knn_most_scratch(B, N, Dk));
   double scan = HUGE_VAL;
-  if (M <= lim) {
+  if (M <= knn_scan_limit(Dk, k)) {
     p.sc = knn_scan_plan(B, M, N, Dk);
     p.scratch = (size_t)(B * M * p.sc.ngroups) * 4;
-    // its maxima take no more than a copy of the rows would (or 64 MiB)
-    const size_t most = std::max((size_t)(B * kpad(N) * Dk) * 2, (size_t)64 << 20);
-    if (p.scratch <= std::min(scratch, most)) scan = knn_scan_us(B, M, N, Dk, k, p.sc);
+    if (p.scratch <= scratch) scan = knn_scan_us(B, M, N, Dk, k, p.sc);
   }
   p.scan = scan <= knn_list_us(1, 1, 1, Dk, k, 1);  // less than the list kernel takes at the least
   if (p.scan) return p;
@@ -453,10 +459,22 @@ static KnnWs knn_carve(void* base, int64_t B, int64_t M, int64_t N, int64_t D) {
   return w;
 }
 
+// Scratch for every route that knn_plan can choose for these sizes or for fewer
+// queries or rows: the largest number of groups and of shares, not the plan's own,
+// so a workspace of the largest sizes a program meets serves all its calls.
+static size_t knn_scratch_bytes(int64_t B, int64_t M, int64_t N, int64_t Dk, int k) {
+  const int64_t pairs = ((N + 31) / 32 + 1) / 2;  // a group is two tiles or more
+  const int64_t groups = std::min<int64_t>(pairs, KNN_MAX_GROUPS);
+  const int64_t shares = std::min<int64_t>(kpad(N) / (Dk <= 128 ? 128 : 64), KNN_MAX_SPLITS);
+  const size_t maxima = (size_t)(B * std::min(M, knn_scan_limit(Dk, k)) * groups) * 4;
+  const size_t lists = shares > 1 ? (size_t)(B * M * shares * k) * 8 : 0;
+  return std::min(std::max(maxima, lists), knn_most_scratch(B, N, Dk));
+}
+
 size_t kmeans_knn_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t D, int k, int xdtype) {
   if (knn_check_sizes(B, M, N, D, k, xdtype) != FKM_OK) return 0;
   const KnnWs w = knn_carve(nullptr, B, M, N, D);
-  const size_t want = w.scratch_at + knn_plan(B, M, N, w.Dk, k, SIZE_MAX).scratch;
+  const size_t want = w.scratch_at + knn_scratch_bytes(B, M, N, w.Dk, k);
   return want > w.fixed ? want : w.fixed;
 }
 

@@ -247,9 +247,21 @@ def kmeans_knn(Q: torch.Tensor, R: torch.Tensor, k: int, nbr_idx: Optional[torch
     _need(nbr_idx, "nbr_idx", torch.int32, B * M * k)
     _need(nbr_dist, "nbr_dist", torch.float32, B * M * k)
     need = knn_workspace_bytes(B, M, N, D, k, Q.dtype)
-    if ws is None or ws.numel() < need:
-        ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
-    _need(ws, "ws", torch.uint8)
-    _check(lib.kmeans_knn(_ptr(Q), _ptr(R), _dt(Q), B, M, N, D, int(k), _ptr(nbr_idx),
-                          _ptr(nbr_dist), _ptr(ws), ws.numel(), _stream()), "kmeans_knn")
+
+    def call(buf):
+        return lib.kmeans_knn(_ptr(Q), _ptr(R), _dt(Q), B, M, N, D, int(k), _ptr(nbr_idx),
+                              _ptr(nbr_dist), _ptr(buf), buf.numel(), _stream())
+
+    # A workspace smaller than `need` serves too where the library takes it, with
+    # a slower route; one that it refuses is replaced.
+    enough = ws is not None and ws.numel() >= need
+    if enough or (ws is not None and ws.dtype == torch.uint8 and ws.device == dev and
+                  ws.is_contiguous()):
+        _need(ws, "ws", torch.uint8)
+        rc = call(ws)
+        if enough or rc != ERR_WORKSPACE:
+            _check(rc, "kmeans_knn")
+            return nbr_idx, nbr_dist
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
+    _check(call(ws), "kmeans_knn")
     return nbr_idx, nbr_dist

@@ -270,6 +270,32 @@ def test_knn_route_and_workspace(lib):
     assert _route(lib, 1, 10, 20, 64, 21) == -1 and _route(lib, 1, 10, 20, 64, 4, F32) == -1
 
 
+@pytest.mark.parametrize("N,D,k", [(20_000, 32, 10), (50_000, 32, 16), (300_000, 32, 32), (130, 16, 5),
+                                   (1_000_003, 128, 10), (70, 100, 1), (9_000, 200, 20)])
+@pytest.mark.parametrize("B", [1, 3, 64])
+def test_knn_workspace_grows_with_the_call(lib, B, N, D, k):
+    """A workspace of the largest M or N serves every smaller one by the route that it
+    would take with all the memory there is; beyond a copy of the rows it takes 64 MiB at most."""
+    kw = lambda M, n: lib.kmeans_knn_workspace_bytes(B, M, n, D, k, BF16)
+    up = lambda v: (v + 255) // 256 * 256
+    queries = (1, 100, 128, 1024, 1025, 2048, 2049, 4096, 8192, 8193, 65_536, 131_072, 140_000, 700_000,
+               1_500_000, 2_000_000)
+    last = 0
+    for M in queries:
+        n = kw(M, N)
+        assert n >= last, M
+        last = n
+        copy, Dk = up(B * (N + 127) // 128 * 128 * 2 * ((D + 15) // 16 * 16)), (D + 15) // 16 * 16
+        padded = up(B * M * Dk * 2) + copy if Dk != D else 0
+        assert n <= up(B * (N + 127) * 4) + padded + B * 128 * Dk * 2 + max(copy, 64 << 20) + 8192, M
+        assert _route(lib, B, M, N, D, k, wsb=kw(queries[-1], N)) == _route(lib, B, M, N, D, k), M
+    last = 0
+    for n in sorted({k, 64, 300, 1000, 16_384, 100_000, 262_144, 262_145, 524_288, 524_289, 2_000_000, N}):
+        if n >= k:
+            assert kw(1500, n) >= last, n
+            last = kw(1500, n)
+
+
 def test_calibration_library_exports_its_header():
     """libfkm_calib.so (the benchmark's in-run ceilings) exports every call that
     include/fkm_calib.h declares and rejects bad arguments on the host."""

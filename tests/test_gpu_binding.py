@@ -70,3 +70,30 @@ def test_host_tensors_and_host_workspaces_are_refused(km):
     with pytest.raises(ValueError, match="contiguous"):
         km.kmeans_assign(X.transpose(1, 2).contiguous().transpose(1, 2), C)
     torch.cuda.synchronize()
+
+
+def test_knn_workspaces_are_used_as_given(km):
+    """A workspace of the largest call, and one of a copy of the rows, are passed on as they
+    are: nothing is allocated.  One that is too small is replaced."""
+    g = torch.Generator().manual_seed(5)
+    N, D, k = 20_000, 32, 10
+    R = torch.randn((1, N, D), generator=g).to(torch.bfloat16).cuda()
+    Q = torch.randn((1, 4096, D), generator=g).to(torch.bfloat16).cuda()
+    want = km.kmeans_knn(Q, R, k)
+    up = lambda v: (v + 255) // 256 * 256  # noqa: E731
+    Np = (N + 127) // 128 * 128
+    least = up(Np * D * 2) + up(Np * 4)
+    for size in (km.knn_workspace_bytes(1, 131_072, N, D, k, Q.dtype), least):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        for M in (1, 100, 2048, 2049, 4096):
+            q = Q[:, :M].contiguous()
+            i = torch.empty((1, M, k), dtype=torch.int32, device="cuda")
+            d = torch.empty((1, M, k), device="cuda")
+            torch.cuda.synchronize()
+            before = torch.cuda.memory_stats()["allocation.all.allocated"]
+            km.kmeans_knn(q, R, k, nbr_idx=i, nbr_dist=d, ws=ws)
+            assert torch.cuda.memory_stats()["allocation.all.allocated"] == before, (size, M)
+            assert torch.equal(i, want[0][:, :M]) and torch.equal(d, want[1][:, :M])
+    tiny = torch.empty(256, dtype=torch.uint8, device="cuda")
+    i, d = km.kmeans_knn(Q, R, k, ws=tiny)
+    assert torch.equal(i, want[0]) and torch.equal(d, want[1])
