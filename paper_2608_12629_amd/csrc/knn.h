@@ -72,31 +72,48 @@ __global__ __launch_bounds__(256) void knn_norm_kernel(const uint4* __restrict__
 
 // Database rows to the staged layout: row j of each instance to chat (padded to
 // Np rows: zero rows with score -FLT_MAX; rows of Din elements widened to D
-// with zeros), and its -|r|^2/2 (one wave per row, lane-strided then a fixed
-// xor butterfly).
+// with zeros), and its -|r|^2/2.  A lane takes one 16-byte chunk of a row and a
+// group of prep_lanes(D) lanes the row; the norm's chunks are added in the order of
+// tree_sumsq, as by the kernels that read rows in place and by the scan, so a
+// search has the same bits on every route.
+__host__ __device__ inline int prep_lanes(int D) {
+  int g = 2;
+  while (g < D / 8) g *= 2;
+  return g;
+}
 template <int DT>
 __global__ __launch_bounds__(256) void knn_prep_kernel(const uint16_t* __restrict__ R, int64_t B,
                                                        int N, int Np, int Din, int D,
                                                        uint16_t* __restrict__ chat,
                                                        float* __restrict__ cinit) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= B * Np) return;
+  const int g = prep_lanes(D), rc = D / 8, half = rc / 2;
+  const int lane = threadIdx.x & 63, l = threadIdx.x % g;  // l: the lane's chunk
+  const int64_t row = (int64_t)blockIdx.x * (256 / g) + threadIdx.x / g;
+  if (row >= B * Np) return;  // whole groups
   const int64_t b = row / Np;
   const int j = (int)(row % Np);
   const bool pad = j >= N;
-  const uint16_t* r = R + (b * N + (pad ? 0 : j)) * Din;
-  uint16_t* out = chat + row * D;
-  float ss = 0.f;
-  for (int d = lane; d < D; d += 64) {
-    const uint16_t h = (pad || d >= Din) ? (uint16_t)0 : r[d];
-    out[d] = h;
-    const float v = Elem<DT>::widen(h);
-    ss = __builtin_fmaf(v, v, ss);
-  }
+  uint4 q = make_uint4(0, 0, 0, 0);
+  if (!pad && l < rc) {
+    const uint16_t* r = R + (b * N + j) * Din;
+    if (8 * l + 8 <= Din) {
+      __builtin_memcpy(&q, r + 8 * l, 16);  // rows of any Din start at any 2-byte boundary
+    } else {
+      uint16_t h[8];
 #pragma unroll
-  for (int m = 1; m < 64; m <<= 1) ss += __shfl_xor(ss, m);
-  if (lane == 0) cinit[row] = pad ? -0x1.fffffep127f : -0.5f * ss;
+      for (int e = 0; e < 8; ++e) h[e] = 8 * l + e < Din ? r[8 * l + e] : (uint16_t)0;
+      __builtin_memcpy(&q, h, 16);
+    }
+  }
+  if (l < rc) *reinterpret_cast<uint4*>(chat + row * D + 8 * l) = q;
+  float ss = chunk_sumsq<DT>(q, 0.f);
+  const int c = l < half ? l : l - half;
+  for (int d = 1; d < half; d *= 2) {
+    const float v = __shfl(ss, lane + d);
+    if (c % (2 * d) == 0 && c + d < half) ss += v;
+  }
+  const float v = __shfl(ss, lane + half);
+  if (l == 0) cinit[row] = pad ? -0x1.fffffep127f : -0.5f * (ss + v);
 }
 
 // Insert (s, i) into a best-first list: a compare-exchange pass down the list
@@ -458,7 +475,8 @@ hipError_t launch_knn_norm(const void* R, int64_t B, int64_t N, int64_t Np, int6
 template <int DT>
 hipError_t launch_knn_prep(const void* R, int64_t B, int64_t N, int64_t Np, int64_t Din, int64_t D,
                            void* chat, float* cinit, hipStream_t s) {
-  knn_prep_kernel<DT><<<dim3((unsigned)((B * Np + 3) / 4)), 256, 0, s>>>(
+  const int64_t rows = 256 / prep_lanes((int)D);  // per workgroup
+  knn_prep_kernel<DT><<<dim3((unsigned)((B * Np + rows - 1) / rows)), 256, 0, s>>>(
       (const uint16_t*)R, B, (int)N, (int)Np, (int)Din, (int)D, (uint16_t*)chat, cinit);
   return hipGetLastError();
 }

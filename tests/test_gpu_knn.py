@@ -11,6 +11,7 @@ rows, as for the assignment's exemption of near-ties.
 """
 from __future__ import annotations
 
+import ctypes
 import sys
 
 import numpy as np
@@ -108,28 +109,35 @@ def test_knn_parity(km, oracle, shape):
     say(f"  positions differing from the oracle's order (near-ties): {differ} of {B * M * k}")
 
 
-# Sizes at the edges of the routes: the scan's group sizes, splits and partial
-# groups (few queries), and the list kernel's shares (more queries).
+# Sizes at the edges of the routes, and the route of each: 0 the scan (its group
+# sizes, splits and partial groups), else the list kernel's shares.
 ROUTES = [
-    (1, 1, 32, 16, 32, "bf16"),           # one tile, one group, k = N
-    (1, 1, 33, 128, 32, "f16"),           # a row in the second tile, fewer groups than k
-    (1, 3, 4095, 144, 32, "bf16"),        # 64-row stages, every group chosen by some query
-    (2, 129, 20_001, 64, 16, "f16"),      # two query blocks, ragged last group, batched
-    (1, 5, 300_007, 32, 10, "bf16"),      # 4,689 groups of two tiles
-    (1, 2, 530_000, 16, 9, "f16"),        # more than 8,192 pairs of tiles: groups of four
-    (1, 40, 9_000, 40, 12, "bf16"),       # padded rows (40 -> 48)
-    (1, 2_049, 1_500, 32, 10, "bf16"),    # the list kernel in shares
-    (1, 1_025, 900, 144, 20, "f16"),      # the scan at k > 16 past the limit of smaller k
-    (2, 2_100, 700, 24, 16, "f16"),       # shares, padded rows, batched
+    (1, 1, 32, 16, 32, "bf16", 0),           # one tile, one group, k = N
+    (1, 1, 33, 128, 32, "f16", 0),           # a row in the second tile, fewer groups than k
+    (1, 3, 4095, 144, 32, "bf16", 0),        # 64-row stages, every group chosen by some query
+    (2, 129, 20_001, 64, 16, "f16", 0),      # two query blocks, ragged last group, batched
+    (1, 5, 300_007, 32, 10, "bf16", 0),      # 4,689 groups of two tiles
+    (1, 2, 530_000, 16, 9, "f16", 0),        # more than 8,192 pairs of tiles: groups of four
+    (1, 40, 9_000, 40, 12, "bf16", 0),       # padded rows (40 -> 48)
+    (2, 7, 3_001, 100, 3, "f16", 0),         # padded rows (100 -> 112), batched
+    (1, 9, 2_000, 250, 10, "bf16", 0),       # padded rows (250 -> 256), 64-row stages
+    (1, 2_049, 1_500, 32, 10, "bf16", 12),   # the list kernel in shares
+    (1, 1_025, 900, 144, 20, "f16", 16),     # its 32-entry lists, 64-row stages
+    (1, 700, 4_000, 144, 20, "f16", 0),      # the same by the scan
+    (2, 2_100, 700, 24, 16, "f16", 6),       # shares, padded rows, batched
+    (1, 5, 200, 1, 4, "bf16", 0),            # one element a row (1 -> 16)
 ]
 
 
 @pytest.mark.parametrize("shape", ROUTES, ids=lambda s: "x".join(map(str, s)))
 def test_knn_routes(km, oracle, shape):
-    """Every route against fp64, and the unsplit list kernel (what a workspace
-    of a copy of the rows leaves room for) against the others bit for bit
-    where the rows are read in place."""
-    B, M, N, D, k, dt = shape
+    """Every route against fp64, and against the others bit for bit: the same
+    queries among so many that the list kernel takes them in shares, and with
+    the least workspace that is accepted, which leaves some calls no room but
+    for the unsplit list kernel."""
+    B, M, N, D, k, dt, route = shape
+    took = lambda m, n: km.lib.fkm_knn_route(*map(ctypes.c_int64, (B, m, N, D)), k, km._dt(Qd),  # noqa: E731
+                                             ctypes.c_size_t(n))
     Q, R = _data(B, M, N, D, dt, seed=M + N + k)
     say(f"[knn routes] B={B} M={M} N={N} D={D} k={k} {dt}")
     Qd, Rd = Q.cuda(), R.cuda()
@@ -148,20 +156,22 @@ def test_knn_routes(km, oracle, shape):
         tol = 4 * (D + 8) * 2.0 ** -24 * (scale + (r64[b] ** 2).sum(-1).max())
         assert ((got - want).abs() <= tol).all(), float(((got - want).abs() / tol).max())
         assert ((gd[b].cpu().double() - got.clamp(min=0)).abs() <= tol).all()
+    assert took(M, km.knn_workspace_bytes(B, M, N, D, k, Qd.dtype)) == route
     # the least workspace: row scores and copies, no room for shares or maxima beyond a row copy
     up = lambda v: (v + 255) // 256 * 256  # noqa: E731
     Np, Dk = (N + 127) // 128 * 128, (D + 15) // 16 * 16
     least = up(B * Np * Dk * 2) + up(B * Np * 4) + (up(B * M * Dk * 2) if Dk != D else 0)
     assert km.knn_workspace_bytes(B, M, N, D, k, Qd.dtype) >= least
-    li, ld = torch.empty_like(gi), torch.empty_like(gd)
-    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
-    km._check(km.lib.kmeans_knn(km._ptr(Qd), km._ptr(Rd), km._dt(Qd), B, M, N, D, k, km._ptr(li),
-                                km._ptr(ld), km._ptr(ws), ws.numel(), km._stream()), "kmeans_knn")
-    torch.cuda.synchronize()
-    if Dk == D:
-        assert torch.equal(li, gi) and torch.equal(ld, gd)
-    else:  # the padded rows' norms are summed in another order on the list kernel
-        assert (ld - gd).abs().max() <= tol.max()
+    if Dk != D:
+        assert took(M, least) == 1
+    li, ld = km.kmeans_knn(Qd, Rd, k, ws=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(li, gi) and torch.equal(ld, gd)
+    if route == 0:
+        many = {False: 2049, True: 8193}[k > 16] if Dk <= 128 else {False: 1025, True: 4097}[k > 16]
+        assert took(many, 1 << 50) > 0
+        Qm = Qd.repeat(1, (many + M - 1) // M, 1)[:, :many].contiguous()
+        li, ld = km.kmeans_knn(Qm, Rd, k)
+        assert torch.equal(li[:, :M], gi) and torch.equal(ld[:, :M], gd)
 
 
 def test_knn_duplicate_rows(km):
