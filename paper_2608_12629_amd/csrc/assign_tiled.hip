@@ -47,20 +47,14 @@
 // so every stage issues the same loads and runs the same code: its MFMAs add
 // a finite x times zero, which is exactly zero.
 //
-// Super-tiles give every XCD whole groups of 8 point blocks, so calls whose
-// point blocks fall short of a multiple of 64 by more than an eighth load the
-// XCDs unevenly: they go plainly in point-block order (79 blocks: 20,000 x
-// 1,024, K = 16,384: 900 -> 613 us; 32 x 20,000 x 512, K = 2,000: 2,049 ->
-// 1,426; 391 blocks: 437 -> 408; 196 blocks: 428 -> 434; but 2,048 blocks, 512k
-// x 1,024, K = 16,384, whose operands the XCDs' L2 then no longer share: 14.5
-// -> 16.0 ms).  Calls that would leave CUs idle take fewer centroid blocks per
-// workgroup (tiled_group; the same bits).  Both together: 2,000 x 512, K =
-// 2,000: 106 -> 30 us; 10,000 x 512: 109 -> 46; 20,000 x 512: 116 -> 64.
-//
 // Block order is XCD-aware: workgroup ids go round-robin over the 8 XCDs, and
 // each XCD walks super-tiles of 8 point blocks x all centroid groups (point
 // block fastest), so the workgroups resident on an XCD share both operands
-// through that XCD's L2.
+// through that XCD's L2.  Where that loads the XCDs too unevenly, the blocks go
+// plainly in point-block order (tiled_plain).  Calls that would leave CUs idle
+// take fewer centroid blocks per workgroup (tiled_group; the same bits).  Both
+// together: 2,000 x 512, K = 2,000: 106 -> 30 us; 10,000 x 512: 109 -> 46;
+// 20,000 x 512: 116 -> 64.
 #include <algorithm>
 
 #include "fkm_device.h"
@@ -487,6 +481,19 @@ static int tiled_group(int64_t point_blocks, int ncb) {
   return best;
 }
 
+// Plain point-block order, where the first XCD, which gets every super-tile's
+// first group of 8 point blocks, would have a fifth more of them than an eighth
+// (a ninth, where the centroids fit an XCD's 4 MiB of L2 and their sharing is worth
+// less).  Measured, super-tiles -> plain, us: 79 point blocks (1.62 times an
+// eighth) x 1,024 elements, K = 16,384: 896 -> 637; 150 (1.28): 1,346 -> 1,228;
+// but 196 (1.14): 1,496 -> 1,584; 385 (1.02): 2,816 -> 3,108; 455 (1.11) x 2,048,
+// K = 8,192: 3,535 -> 3,956; 2,048 (1): 14.5 -> 16.0 ms.  With 4 MiB of centroids
+// (512, K = 4,096): 398 (1.13): 444 -> 406; 196: 228 -> 233; 257 (1.03): 297 -> 309.
+static bool tiled_plain(int npb, int64_t centroid_bytes) {
+  const int64_t first = npb / 64 * 8 + std::min(npb % 64, 8);
+  return 800 * first > (centroid_bytes <= (4 << 20) ? 111 : 120) * (int64_t)npb;
+}
+
 hipError_t launch_assign_tiled(const void* X, int dt, const Workspace& w, int64_t B, int64_t N,
                                int64_t D, int32_t* idx, float* min_dist, hipStream_t s) {
   if (D % DC != 0 || w.Kp % BC != 0) return hipErrorInvalidValue;
@@ -510,7 +517,7 @@ hipError_t launch_assign_tiled(const void* X, int dt, const Workspace& w, int64_
   const int cbpg = tiled_group(B * npb, ncb);
   const int ncbg = (ncb + cbpg - 1) / cbpg;
   int npb64 = (npb + 63) / 64 * 64;  // whole super-tiles on every XCD
-  const bool plain = 8 * (int64_t)npb64 > 9 * (int64_t)npb;
+  const bool plain = tiled_plain(npb, w.Kp * D * 2);
   if (plain) npb64 = npb;
   const dim3 grid((unsigned)(npb64 * ncbg), (unsigned)B);
   if (dt == DT_BF16)

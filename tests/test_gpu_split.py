@@ -63,6 +63,25 @@ def test_shared_centroids_same_bits(km, N, D, K, dt, B):
     assert torch.equal(Cb1.view(torch.int32), C1.view(torch.int32).expand(B, K, D))
 
 
+# rows past 256 elements: point blocks in either order (79 and 136 plain, 258 in
+# super-tiles, 60 in one), few enough for fewer centroid blocks a workgroup: a
+# point's bits do not depend on the others of its call
+@pytest.mark.parametrize("D,K", [(288, 300), (320, 2100)])
+def test_wide_block_orders_same_bits(km, D, K):
+    g = torch.Generator(device="cuda").manual_seed(D)
+    X = torch.randn((1, 66_000, D), generator=g, device="cuda").to(torch.bfloat16)
+    C = torch.randn((1, K, D), generator=g, device="cuda")
+    idx, md = km.kmeans_assign(X, C)
+    for N in (1, 256, 2_049, 15_300, 20_001, 34_600, 50_100, 65_800):
+        i, m = km.kmeans_assign(X[:, :N].contiguous(), C)
+        assert torch.equal(i, idx[:, :N]) and torch.equal(m, md[:, :N]), N
+    n = 2_000  # and the bits are those of the nearest centroids
+    x, c = X[0, -n:].double(), C[0].to(torch.bfloat16).double()
+    d = (x * x).sum(1)[:, None] - 2 * x @ c.T + (c * c).sum(1)[None]
+    got = d.gather(1, idx[0, -n:].long()[:, None])[:, 0]
+    assert bool((got - d.min(1).values <= 1e-3 * (x * x).sum(1)).all())
+
+
 # the update's sort: one pass (9 and 10 bits, a chunk, a chunk and one), the
 # largest one-bit-short and full digit, two passes from 1,025 clusters on and
 # where a batch has too many bins; every K with ids outside [0, K) among idx
