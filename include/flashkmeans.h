@@ -51,12 +51,14 @@
  *   FKM_ERR_UNSUPPORTED means valid but outside what this build implements:
  *   not gfx950; D > 2048; fp32 D > 256; K > 65536; N > 2^31-1; B > 65535.
  * - Row widths: the kernels take D a multiple of 16 (and, for bf16/fp16 rows
- *   wider than 256, of 32).  Any other D is served through copies of the
- *   points and centroids in zero-padded rows of the next such width, made in
- *   the workspace at the start of each call (once per kmeans_lloyd call):
- *   zeros change no distance, sum or norm, so the results are those of the
- *   unpadded rows, at the cost of that copy.  (bf16/fp16 rows of at most 16
- *   elements are copied into fp32 rows of 16, see above.)
+ *   wider than 256, of 32).  kmeans_assign reads the centroids of any D in
+ *   place, and bf16/fp16 points of D = 17 .. 256 too, except for few clusters
+ *   (D of 17 .. 96, K of at most 256).  Any other D is served through copies
+ *   of the points and centroids in zero-padded rows of the next such width,
+ *   made in the workspace at the start of each call (once per kmeans_lloyd
+ *   call): zeros change no distance, sum or norm, so the results are those of
+ *   the unpadded rows, at the cost of that copy.  (bf16/fp16 rows of at most
+ *   16 elements are copied into fp32 rows of 16, see above.)
  *   FKM_ERR_HIP reports a failed HIP call or launch.  No C++ exception
  *   crosses this boundary.
  */
