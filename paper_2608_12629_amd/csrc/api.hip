@@ -338,28 +338,31 @@ static KnnScanPlan knn_scan_plan(int64_t B, int64_t M, int64_t N, int64_t Dk) {
   return p;
 }
 
-// What the routes take, in us: fitted to times over B = 1 .. 100, M = 1 .. 8,192, N
-// = 64 .. 1,000,000, D = 16 .. 256, k = 1 .. 32, bf16 (1,961 shapes; the list
-// kernel within 17%, one standard deviation, the scan too).
+// What the routes take, in us: fitted to times over B = 1 .. 100, M = 1 .. 70,000,
+// N = 40 .. 1,000,000, D = 16 .. 256, k = 1 .. 32, bf16 (3,161 shapes; the list
+// kernel within 12%, one standard deviation, the scan within 20%).
 //
 // The list kernel over s shares of the rows: rounds of resident workgroups (a
-// chip more than half full of those with up to 16 entries runs 1.2 times slower),
-// each its stages and the filling of its lists, whose insertions thin out as
-// the lists improve (about the root of the stages); and for a split the merge,
-// a step per entry, whose throughput counts for many queries.
+// chip more than half full of those with up to 16 entries runs 1.22 times
+// slower; the last, partial round costs less than a whole one), each its stages
+// and the filling of its lists, whose insertions thin out as the lists improve
+// (about the root of the stages); and for a split the merge, a step per entry,
+// whose throughput counts for many queries.
 static double knn_list_us(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, int64_t s) {
   const bool wide = Dk > 128, large = k > 16;
   const int64_t nst = kpad(N) / (wide ? 64 : 128), n = (nst + s - 1) / s;
   const int64_t qpb = !large && !wide ? 256 : 128;  // queries per workgroup
   const int64_t slots = large ? 256 : 512;           // resident workgroups
   const int64_t wgs = (M + qpb - 1) / qpb * B * s;
-  const double rounds = (double)((wgs + slots - 1) / slots);
-  const double load = large ? rounds : 2 * wgs <= slots ? 1.0 : 1.2 * rounds;
+  const double rounds = std::max(1.0, 0.7 * (double)((wgs + slots - 1) / slots) +
+                                          0.3 * (double)wgs / (double)slots);
+  const double load = large ? rounds : 2 * wgs <= slots ? 1.0 : 1.22 * rounds;
   const int entries = k <= 8 ? 8 : k <= 10 ? 10 : k <= 16 ? 16 : KNN_MAX_K;
-  const double stage = (wide ? 1.4 : 1.3 + 1.4 * (double)Dk / 128) * (large ? 1.25 : 1.0);
-  const double fill = (wide ? (large ? 2.1 : 1.67) : large ? 3.1 : 3.85) * entries;
-  double us = load * (1.3 + stage * (double)n + fill * (std::sqrt((double)n) - 0.05));
-  if (s > 1) us += 5 + k + (double)(B * M) * 1e-4 * (4 + k) * (wide ? 1.8 : 1.0);
+  const double stage = (wide ? 0.5 + 0.9 * (double)Dk / 256 : 1.2 + 1.2 * (double)Dk / 128) *
+                       (large ? 1.65 : 1.0);
+  const double fill = (wide ? (large ? 2.03 : 1.73) : large ? 3.1 : 4.0) * entries;
+  double us = load * (0.6 + stage * (double)n + fill * (std::sqrt((double)n) - 0.05));
+  if (s > 1) us += 7.5 + 0.9 * k + (double)(B * M) * 1e-4 * (4 + 0.85 * k) * (wide ? 1.6 : 1.0);
   return us;
 }
 
@@ -368,18 +371,18 @@ static double knn_list_us(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, in
 // elements); with fewer groups than k every row is ranked against every other.
 static double knn_scan_us(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, const KnnScanPlan& p) {
   const bool wide = Dk > 128;
-  const int64_t nst = kpad(N) / (wide ? 64 : 128);
+  const int64_t nst = kpad(N) / p.tcs;
   const double tiles = (double)(std::min<int64_t>(k, p.ngroups) << p.gs);
-  double pick = wide ? 0.025 + 0.00117 * tiles : 0.0213 + 0.00065 * tiles;
-  if (p.ngroups < k) pick += 5.4e-5 * (double)(N * ((N + 511) / 512));  // 512 threads
+  double pick = wide ? 0.0233 + 0.00116 * tiles : 0.0195 + 0.00068 * tiles;
+  if (p.ngroups < k) pick += 5.6e-5 * (double)(N * ((N + 511) / 512));  // 512 threads
   if (Dk <= 32) pick /= 3;
-  const double stage = 0.2 + 2.85 * (double)std::min<int64_t>(Dk, 128) / 128;
-  return 8.5 + std::max(7.0, (double)(B * M) * pick) +
+  const double stage = 0.25 + 2.8 * (double)(p.tcs * Dk) / (128 * 128);
+  return 9 + std::max(7.0, (double)(B * M) * pick) +
          (double)((M + 127) / 128 * B * nst) / 512 * stage;
 }
 
 // The route of a search.  The list kernel's shares: the number of the least
-// estimate, where that saves a tenth (65,536 queries in 1,048,576 x 128, k = 10:
+// estimate, where that saves a twentieth (65,536 queries in 1,048,576 x 128, k = 10:
 // 18,291 us unsplit, 15,690 in 2 shares, 17,854 in 3; 4,096 in 100,000: 3,276
 // unsplit, 342 in 32; but 16 x 4,096 in 300: 77 unsplit, 180 in 2).  The scan
 // where it is estimated faster than that (100 queries in 1,000,003 x 128, k = 10:
@@ -417,7 +420,7 @@ static KnnPlan knn_plan(int64_t B, int64_t M, int64_t N, int64_t Dk, int k, size
     const double us = knn_list_us(B, M, N, Dk, k, s);
     if (us < list) list = us, p.splits = (int)s;
   }
-  if (list > 0.9 * whole) list = whole, p.splits = 1;
+  if (list > 0.95 * whole) list = whole, p.splits = 1;
   p.scan = scan <= list;
   if (!p.scan) p.scratch = p.splits > 1 ? p.splits * one : 0;
   return p;
@@ -478,8 +481,9 @@ size_t kmeans_knn_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t D, in
   return want > w.fixed ? want : w.fixed;
 }
 
-// For tests, not in the public header: the route of a search with a workspace of
-// ws_bytes; 0 the scan, else the list kernel's shares of the rows; -1 refused.
+// For the binding and tests, not in the public header: the route of a search with
+// a workspace of ws_bytes; 0 the scan, else the list kernel's shares of the rows; -1
+// refused.
 int fkm_knn_route(int64_t B, int64_t M, int64_t N, int64_t D, int k, int xdtype, size_t ws_bytes) {
   if (knn_check_sizes(B, M, N, D, k, xdtype) != FKM_OK) return -1;
   const KnnWs w = knn_carve(nullptr, B, M, N, D);

@@ -43,6 +43,7 @@ def _load() -> ctypes.CDLL:
     lib.kmeans_knn_workspace_bytes.argtypes = [i64, i64, i64, i64, i32, i32]
     lib.kmeans_knn_workspace_bytes.restype = sz
     lib.kmeans_knn.argtypes = [vp, vp, i32, i64, i64, i64, i64, i32, vp, vp, vp, sz, vp]
+    lib.fkm_knn_route.argtypes = [i64, i64, i64, i64, i32, i32, sz]  # the route a search takes
     for f in (lib.kmeans_assign, lib.kmeans_update, lib.kmeans_lloyd, lib.kmeans_lloyd_noalloc,
               lib.kmeans_knn):
         f.restype = ctypes.c_int
@@ -247,21 +248,17 @@ def kmeans_knn(Q: torch.Tensor, R: torch.Tensor, k: int, nbr_idx: Optional[torch
     _need(nbr_idx, "nbr_idx", torch.int32, B * M * k)
     _need(nbr_dist, "nbr_dist", torch.float32, B * M * k)
     need = knn_workspace_bytes(B, M, N, D, k, Q.dtype)
-
-    def call(buf):
-        return lib.kmeans_knn(_ptr(Q), _ptr(R), _dt(Q), B, M, N, D, int(k), _ptr(nbr_idx),
-                              _ptr(nbr_dist), _ptr(buf), buf.numel(), _stream())
-
-    # A workspace smaller than `need` serves too where the library takes it, with
-    # a slower route; one that it refuses is replaced.
-    enough = ws is not None and ws.numel() >= need
-    if enough or (ws is not None and ws.dtype == torch.uint8 and ws.device == dev and
-                  ws.is_contiguous()):
-        _need(ws, "ws", torch.uint8)
-        rc = call(ws)
-        if enough or rc != ERR_WORKSPACE:
-            _check(rc, "kmeans_knn")
-            return nbr_idx, nbr_dist
-    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
-    _check(call(ws), "kmeans_knn")
+    if ws is None or (ws.numel() < need and not _knn_takes(ws, B, M, N, D, k, Q)):
+        ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
+    _need(ws, "ws", torch.uint8)
+    _check(lib.kmeans_knn(_ptr(Q), _ptr(R), _dt(Q), B, M, N, D, int(k), _ptr(nbr_idx),
+                          _ptr(nbr_dist), _ptr(ws), ws.numel(), _stream()), "kmeans_knn")
     return nbr_idx, nbr_dist
+
+
+def _knn_takes(ws: torch.Tensor, B: int, M: int, N: int, D: int, k: int, Q: torch.Tensor) -> bool:
+    """Whether a workspace of less than ``knn_workspace_bytes`` serves all the same (by a
+    slower route, with the same results)."""
+    return (ws.dtype == torch.uint8 and ws.device == Q.device and ws.is_contiguous() and
+            ws.data_ptr() % 16 == 0 and
+            lib.fkm_knn_route(B, M, N, D, int(k), _dt(Q), ws.numel()) >= 0)

@@ -11,7 +11,6 @@ rows, as for the assignment's exemption of near-ties.
 """
 from __future__ import annotations
 
-import ctypes
 import sys
 
 import numpy as np
@@ -136,8 +135,7 @@ def test_knn_routes(km, oracle, shape):
     the least workspace that is accepted, which leaves some calls no room but
     for the unsplit list kernel."""
     B, M, N, D, k, dt, route = shape
-    took = lambda m, n: km.lib.fkm_knn_route(*map(ctypes.c_int64, (B, m, N, D)), k, km._dt(Qd),  # noqa: E731
-                                             ctypes.c_size_t(n))
+    took = lambda m, n: km.lib.fkm_knn_route(B, m, N, D, k, km._dt(Qd), n)  # noqa: E731
     Q, R = _data(B, M, N, D, dt, seed=M + N + k)
     say(f"[knn routes] B={B} M={M} N={N} D={D} k={k} {dt}")
     Qd, Rd = Q.cuda(), R.cuda()
